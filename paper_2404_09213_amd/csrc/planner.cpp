@@ -125,19 +125,96 @@ int recipe_class(const qsv_plan_t* p, const std::vector<int>& gs) {
     return all_real ? OP_REAL : OP_U2;
 }
 
-int add_recipe(qsv_plan_t* p, const std::vector<int>& gs, bool dagger) {
-    DRecipe r;
-    r.first = (int32_t)p->recipe_gates.size();
-    r.count = (int32_t)gs.size();
-    r.dagger = dagger ? 1 : 0;
-    bool per_sample = false;
-    for (int g : gs) {
-        p->recipe_gates.push_back(g);
-        if (p->gates[g].src == QSV_SRC_INPUT) per_sample = true;
+bool any_input(const qsv_plan_t* p, const std::vector<int>& gs) {
+    for (int g : gs)
+        if (p->gates[g].src == QSV_SRC_INPUT) return true;
+    return false;
+}
+
+int put_gates(qsv_plan_t* p, const std::vector<int>& gs) {
+    const int at = (int)p->recipe_gates.size();
+    p->recipe_gates.insert(p->recipe_gates.end(), gs.begin(), gs.end());
+    return at;
+}
+
+// Appends a recipe with its `slots` consecutive matrix slots; returns the first slot.
+int put_recipe(qsv_plan_t* p, DRecipe& r, bool per_sample, int slots) {
+    r.dir = p->dir;
+    if (per_sample) {
+        r.out = -p->n_ps_mats[p->dir] - 1;
+        p->n_ps_mats[p->dir] += slots;
+    } else {
+        r.out = p->n_shared_mats[p->dir];
+        p->n_shared_mats[p->dir] += slots;
     }
-    r.out = per_sample ? -(p->n_ps_mats++) - 1 : p->n_shared_mats++;
     p->recipes.push_back(r);
     return r.out;
+}
+
+int add_recipe(qsv_plan_t* p, const std::vector<int>& gs, bool dagger) {
+    DRecipe r;
+    std::memset(&r, 0, sizeof r);
+    r.kind = RC_MATRIX;
+    r.first = put_gates(p, gs);
+    r.count = (int32_t)gs.size();
+    r.dagger = dagger ? 1 : 0;
+    return put_recipe(p, r, any_input(p, gs), 1);
+}
+
+// Shear of a rotation core (RC_SHEAR).
+int add_shear(qsv_plan_t* p, const std::vector<int>& gs, int core, bool dagger) {
+    DRecipe r;
+    std::memset(&r, 0, sizeof r);
+    r.kind = RC_SHEAR;
+    r.first = put_gates(p, gs);
+    r.count = (int32_t)gs.size();
+    r.dagger = dagger ? 1 : 0;
+    r.core = core;
+    return put_recipe(p, r, any_input(p, gs), 1);
+}
+
+// P^dagger of `core` times the product of `gs` (RC_VMAT).
+int add_vmat(qsv_plan_t* p, const std::vector<int>& gs, const std::vector<int>& core) {
+    DRecipe r;
+    std::memset(&r, 0, sizeof r);
+    r.kind = RC_VMAT;
+    r.first = put_gates(p, gs);
+    r.count = (int32_t)gs.size();
+    r.first2 = put_gates(p, core);
+    r.count2 = (int32_t)core.size();
+    r.core = CORE_GEN;
+    return put_recipe(p, r, any_input(p, gs) || any_input(p, core), 1);
+}
+
+// A diagonal factor waiting to be applied (host form of DFactor).
+struct Factor {
+    int kind, pos, core;
+    bool dagger;
+    std::vector<int> gates;
+};
+
+// Product of factors (RC_DVEC).
+int add_factors(qsv_plan_t* p, const std::vector<Factor>& fs) {
+    DRecipe r;
+    std::memset(&r, 0, sizeof r);
+    r.kind = RC_DVEC;
+    bool per_sample = false;
+    std::vector<DFactor> d;
+    for (const Factor& f : fs) {
+        DFactor x;
+        x.kind = f.kind;
+        x.pos = f.pos;
+        x.first = put_gates(p, f.gates);
+        x.count = (int32_t)f.gates.size();
+        x.dagger = f.dagger ? 1 : 0;
+        x.core = f.core;
+        d.push_back(x);
+        per_sample |= any_input(p, f.gates);
+    }
+    r.first = (int32_t)p->factors.size();
+    r.count = (int32_t)d.size();
+    p->factors.insert(p->factors.end(), d.begin(), d.end());
+    return put_recipe(p, r, per_sample, 4);
 }
 
 std::vector<Block> split(const qsv_plan_t* p, const std::vector<int>& seq, int k) {
@@ -416,6 +493,8 @@ struct Unit {
     uint32_t D = 0, C = 0;
     int qubit = -1;          // chain qubit, or target of a 2-qubit gate
     int comps = 0;           // backward chain: Pauli components needed (bit 0 X, 1 Y, 2 Z)
+    int core = CORE_NONE;    // rotation-core form: gates [lead, tail) are the core, the others diagonal
+    int lead = 0, tail = 0;
 };
 
 // Generator axis of a parametric gate (0 X, 1 Y, 2 Z).
@@ -557,6 +636,142 @@ std::vector<Unit> bwd_units(const qsv_plan_t* p, const std::vector<int>& gates, 
     return units;
 }
 
+bool is_diag_kind(int k) { return k == QSV_Z || k == QSV_RZ; }
+
+// Sub-list of a chain's gates as a unit of its own.
+Unit sub_unit(const qsv_plan_t* p, const Unit& u, int a, int b) {
+    Unit x;
+    x.qubit = u.qubit;
+    for (int j = a; j < b; ++j) {
+        x.gates.push_back(u.gates[j]);
+        uint32_t D, C;
+        gate_sets(p->gates[u.gates[j]], D, C);
+        x.D |= D;
+        x.C |= C;
+    }
+    x.C &= ~x.D;
+    return x;
+}
+
+// Marks a run of 1-qubit gates as lead diagonals, core, trailing diagonals
+// (an all-diagonal run keeps core = CORE_NONE).
+void classify_core(const qsv_plan_t* p, Unit& u) {
+    const int n = (int)u.gates.size();
+    int a = 0, b = n;
+    while (a < n && is_diag_kind(p->gates[u.gates[a]].kind)) ++a;
+    while (b > a && is_diag_kind(p->gates[u.gates[b - 1]].kind)) --b;
+    u.lead = a;
+    u.tail = b;
+    u.core = CORE_NONE;
+    if (a == b) return;
+    bool param = false;
+    for (int j = a; j < b; ++j) param |= p->gates[u.gates[j]].src != QSV_SRC_NONE;
+    const int k = p->gates[u.gates[a]].kind;
+    u.core = !param ? CORE_FIXED
+             : b - a == 1 && k == QSV_RY ? CORE_RY
+             : b - a == 1 && k == QSV_RX ? CORE_RX
+                                         : CORE_GEN;
+}
+
+// Pauli components a chain's gradients need, taken between its core and its
+// trailing diagonals (after P of a general core is undone).
+int core_comps(const qsv_plan_t* p, const Unit& u, int& nparam) {
+    int comps = 0;
+    nparam = 0;
+    for (int j = 0; j < (int)u.gates.size(); ++j) {
+        const qsv_gate& G = p->gates[u.gates[j]];
+        if (G.src == QSV_SRC_NONE) continue;
+        ++nparam;
+        if (j >= u.tail) { comps |= 4; continue; }
+        int sup = 1 << axis_of(G.kind);
+        for (int k = j + 1; k < u.tail; ++k) sup = conj_support(p->gates[u.gates[k]].kind, sup);
+        if (u.core == CORE_GEN) sup = conj_support(QSV_RZ, sup);
+        comps |= sup;
+    }
+    return comps;
+}
+
+// Backward units of the generated kernels, in uncompute order. A run of
+// 1-qubit gates is [lead diagonals] and [core, trailing diagonals]; the latter
+// is one unit when that takes fewer vector operations per amplitude than gate
+// by gate (a shear costs 2 per state, a component 2, a pending diagonal 1 per
+// state when four qubits share its multiplication) and needs no more
+// components than it has angles.
+std::vector<Unit> bwd_core_units(const qsv_plan_t* p, const std::vector<int>& gates, bool fuse) {
+    std::vector<Unit> out;
+    std::vector<int> open(p->W, -1);
+    std::vector<Unit> runs;
+    for (auto it = gates.rbegin(); it != gates.rend(); ++it) {
+        const qsv_gate& G = p->gates[*it];
+        uint32_t D, C;
+        gate_sets(G, D, C);
+        int u = -1;
+        if (!is_multi(G.kind)) u = open[G.q0];
+        if (u < 0) {
+            runs.emplace_back();
+            u = (int)runs.size() - 1;
+            runs[u].qubit = target_of(G);
+            if (!is_multi(G.kind)) open[G.q0] = u;
+            else
+                for (int q = 0; q < p->W; ++q)
+                    if (qmask(G) >> q & 1) open[q] = -1;
+        }
+        runs[u].gates.insert(runs[u].gates.begin(), *it);
+        runs[u].D |= D;
+        runs[u].C |= C;
+    }
+    for (Unit& u : runs) {
+        u.C &= ~u.D;
+        if (is_multi(p->gates[u.gates[0]].kind)) { out.push_back(u); continue; }
+        classify_core(p, u);
+        const int n = (int)u.gates.size();
+        if (u.core == CORE_NONE) { out.push_back(u); continue; }
+        Unit c = sub_unit(p, u, u.lead, n);
+        classify_core(p, c);
+        int nparam = 0;
+        c.comps = core_comps(p, c, nparam);
+        bool one = fuse;
+        if (fuse && (c.core == CORE_GEN || (c.core == CORE_FIXED && c.tail > 1))) {
+            int sep = 0;
+            for (int j = 0; j < c.tail; ++j) {
+                const int k = p->gates[c.gates[j]].kind;
+                sep += k == QSV_RX || k == QSV_RY ? 4 : is_diag_kind(k) ? 2 : k == QSV_X ? 0 : 8;
+                if (p->gates[c.gates[j]].src != QSV_SRC_NONE) sep += 2;
+            }
+            const bool tail = c.tail < (int)c.gates.size();
+            for (int j = c.tail; j < (int)c.gates.size(); ++j)
+                if (p->gates[c.gates[j]].src != QSV_SRC_NONE) { sep += 2; break; }
+            if (tail) sep += 2;
+            const int whole = (c.core == CORE_GEN ? 4 + 4 : 16 + (tail ? 2 : 0)) + 2 * popc((uint32_t)c.comps);
+            one = whole <= sep && popc((uint32_t)c.comps) <= std::max(nparam, 1);
+        }
+        if (c.core == CORE_FIXED && popc((uint32_t)c.comps) > std::max(nparam, 1)) one = false;
+        if (one) {
+            out.push_back(c);
+        } else {
+            // trailing diagonals together, then the core's gates one by one
+            if (c.tail < (int)c.gates.size()) {
+                Unit x = sub_unit(p, c, c.tail, (int)c.gates.size());
+                classify_core(p, x);
+                out.push_back(x);
+            }
+            for (int j = c.tail - 1; j >= 0; --j) {
+                Unit x = sub_unit(p, c, j, j + 1);
+                classify_core(p, x);
+                int np = 0;
+                x.comps = core_comps(p, x, np);
+                out.push_back(x);
+            }
+        }
+        if (u.lead > 0) {
+            Unit x = sub_unit(p, u, 0, u.lead);
+            classify_core(p, x);
+            out.push_back(x);
+        }
+    }
+    return out;
+}
+
 // Greedy stage grouping: each stage's dense qubits fit the register bits.
 std::vector<std::pair<uint32_t, std::vector<int>>> group_stages(const std::vector<Unit>& units) {
     std::vector<std::pair<uint32_t, std::vector<int>>> stages;
@@ -616,6 +831,36 @@ std::vector<std::pair<uint32_t, std::vector<int>>> group_stages(const std::vecto
     return stages;
 }
 
+std::vector<int> sub_gates(const Unit& u, int a, int b) {
+    return std::vector<int>(u.gates.begin() + a, u.gates.begin() + b);
+}
+
+// Diagonals a backward pass has still to multiply in, per qubit, and its
+// OP_DVEC ops with their factors.
+struct Waiting {
+    std::vector<std::vector<Factor>> diag;
+    struct Vec { int op; std::vector<Factor> f; };
+    std::vector<Vec> vecs;
+    explicit Waiting(int W) : diag(W) {}
+};
+
+// Adds the matrix slots that the table-driven kernels have for one pass of a
+// generated plan to p->ref_shared / ref_ps.
+void count_ref_slots(qsv_plan_t* p, const std::vector<Unit>& units, const std::vector<int>& first_on) {
+    auto add = [&](const std::vector<int>& gs) { ++(any_input(p, gs) ? p->ref_ps : p->ref_shared); };
+    for (const Unit& U : units) {
+        const int n = (int)U.gates.size();
+        if (n == 1 && is_zz(p->gates[U.gates[0]].kind)) continue;
+        for (int j = 0; U.comps && j + 1 < n; ++j)
+            if (p->gates[U.gates[j]].src != QSV_SRC_NONE)
+                add(std::vector<int>(U.gates.begin() + j + 1, U.gates.end()));
+        bool starts = !first_on.empty();
+        for (int b = 0; b < p->W && starts; ++b)
+            if ((qmask(p->gates[U.gates[0]]) >> b & 1) && first_on[b] != U.gates[0]) starts = false;
+        if (!starts) add(U.gates);
+    }
+}
+
 // Builds one DPass (tile qubits + stages + ops) from a pass's gate list.
 struct PassBuilder {
     qsv_plan_t* p;
@@ -643,24 +888,35 @@ struct PassBuilder {
             if (tile >> q & 1) { local_of_qubit[q] = j; ps.lq[j++] = W - 1 - q; }
             else { local_of_qubit[q] = -1; ps.oq[k++] = W - 1 - q; }
         }
-        std::vector<Unit> units = backward ? bwd_units(p, gates, !p->opts.bwd_gate_by_gate)
-                                           : fwd_units(p, gates);
+        const bool fuse = !p->opts.bwd_gate_by_gate;
+        const bool cores = backward && p->opts.codegen != 0;  // rotation cores
+        std::vector<Unit> units = cores ? bwd_core_units(p, gates, fuse) : backward ? bwd_units(p, gates, fuse)
+                                                                                     : fwd_units(p, gates);
+        count_ref_slots(p, cores ? bwd_units(p, gates, fuse) : units, first_on);
         auto groups = group_stages(units);
-        ps.stage0 = (int32_t)p->stages.size();
-        ps.n_stages = (int32_t)groups.size();
-        ps.gout0 = (int32_t)p->gouts.size();
-        int nslot = 0;
+        // register qubits of every stage: its dense qubits, padded with the top local bits
+        std::vector<std::vector<int>> stage_regs;
+        std::vector<int> last_in_regs(W, -1);  // last stage holding a qubit in registers
         for (auto& grp : groups) {
-            DStage st;
-            std::memset(&st, 0, sizeof st);
-            // register bits: the stage's dense qubits, padded with the top local bits
             std::vector<int> regs;
             for (int q = 0; q < W; ++q)
                 if (grp.first >> q & 1) regs.push_back(local_of_qubit[q]);
             for (int lb = m - 1; lb >= 0 && (int)regs.size() < kRegBits; --lb)
                 if (std::find(regs.begin(), regs.end(), lb) == regs.end()) regs.push_back(lb);
             std::sort(regs.begin(), regs.end());
-            for (int i = 0; i < kRegBits; ++i) st.reg[i] = regs[i];
+            for (int lb : regs) last_in_regs[W - 1 - ps.lq[lb]] = (int)stage_regs.size();
+            stage_regs.push_back(regs);
+        }
+        Waiting wait(W);
+        ps.stage0 = (int32_t)p->stages.size();
+        ps.n_stages = (int32_t)groups.size();
+        ps.gout0 = (int32_t)p->gouts.size();
+        int nslot = 0;
+        for (int gi = 0; gi < (int)groups.size(); ++gi) {
+            auto& grp = groups[gi];
+            DStage st;
+            std::memset(&st, 0, sizeof st);
+            for (int i = 0; i < kRegBits; ++i) st.reg[i] = stage_regs[gi][i];
             auto pos_of = [&](int qubit) -> int {
                 const int lb = local_of_qubit[qubit];
                 for (int i = 0; i < kRegBits; ++i)
@@ -674,7 +930,115 @@ struct PassBuilder {
             };
             st.op0 = (int32_t)p->ops.size();
             int sign_op = -1;  // open OP_SIGN being extended
-            for (int ui : grp.second) {
+            // -- rotation cores (see CoreKind) --
+            std::vector<char> done_pre(units.size(), 0);   // diagonals before the core applied
+            std::vector<char> done_grad(units.size(), 0);  // gradient components taken
+            // diagonals that a unit needs applied before its core
+            auto pre_factors = [&](const Unit& U) {
+                std::vector<Factor> f;
+                if (U.tail < (int)U.gates.size())
+                    f.push_back({F_DIAG, 0, CORE_NONE, true, sub_gates(U, U.tail, (int)U.gates.size())});
+                if (U.core == CORE_GEN) f.push_back({F_POST, 0, U.core, true, sub_gates(U, U.lead, U.tail)});
+                return f;
+            };
+            auto comp = [&](const Unit& U, int kind, int ctl, int ctl2) {
+                DOp o;
+                std::memset(&o, 0, sizeof o);
+                o.kind = kind;
+                o.pos = pos_of(U.qubit);
+                o.sh = W - 1 - U.qubit;
+                o.ctl = ctl;
+                o.ctl2 = ctl2;
+                o.slot = nslot++;
+                p->ops.push_back(o);
+                return o.slot;
+            };
+            auto gout = [&](int gate, int axis, int c0, int c1, int c2, int mat) {
+                DGOut go;
+                std::memset(&go, 0, sizeof go);
+                go.ord = p->param_ordinal[gate];
+                go.axis = axis;
+                go.c0 = c0;
+                go.c1 = c1;
+                go.c2 = c2;
+                go.mat = mat;
+                p->gouts.push_back(go);
+            };
+            // components and gradient outputs of a core unit, at the point between
+            // its core and its trailing diagonals
+            auto core_grads = [&](const Unit& U) {
+                int slot_of[3] = {-1, -1, -1};
+                for (int a = 0; a < 3; ++a)
+                    if (U.comps >> a & 1) slot_of[a] = comp(U, OP_GX + a, -1, -1);
+                for (int j = 0; j < (int)U.gates.size(); ++j) {
+                    const qsv_gate& G = p->gates[U.gates[j]];
+                    if (G.src == QSV_SRC_NONE) continue;
+                    const int axis = axis_of(G.kind);
+                    if (j >= U.tail || (j == U.tail - 1 && U.core != CORE_GEN)) {
+                        gout(U.gates[j], -1, slot_of[j >= U.tail ? 2 : axis], -1, -1, 0);
+                        continue;
+                    }
+                    const std::vector<int> after = sub_gates(U, j + 1, U.tail);
+                    const int mat = U.core == CORE_GEN ? add_vmat(p, after, sub_gates(U, U.lead, U.tail))
+                                                       : add_recipe(p, after, false);
+                    gout(U.gates[j], axis, slot_of[0], slot_of[1], slot_of[2], mat);
+                }
+            };
+            // Applies everything waiting on this stage's register qubits, with the
+            // diagonals that the next core on each of them needs (from the unit at
+            // position `at` of the stage on), as one multiplication.
+            auto flush = [&](size_t at) {
+                std::vector<Factor> f;
+                std::vector<int> hoisted;
+                int mask = 0;
+                for (int r = 0; r < kRegBits; ++r) {
+                    const int q = W - 1 - ps.lq[st.reg[r]];
+                    auto take = [&](std::vector<Factor> fs) {
+                        for (Factor& x : fs) {
+                            x.pos = r;
+                            mask |= 1 << r;
+                            f.push_back(x);
+                        }
+                    };
+                    take(wait.diag[q]);
+                    wait.diag[q].clear();
+                    // diagonals may move ahead of units that are diagonal on q, the
+                    // components only of units that leave q alone
+                    bool alone = true;
+                    for (size_t j = at; j < grp.second.size(); ++j) {
+                        const int vi = grp.second[j];
+                        const Unit& V = units[vi];
+                        if (!(V.D >> q & 1)) {
+                            if (V.C >> q & 1) alone = false;
+                            continue;
+                        }
+                        if (V.core != CORE_NONE) {
+                            if (!done_pre[vi]) take(pre_factors(V));
+                            done_pre[vi] = 1;
+                            if (alone && !done_grad[vi]) hoisted.push_back(vi);
+                        }
+                        break;
+                    }
+                }
+                if (!f.empty()) {
+                    DOp o;
+                    std::memset(&o, 0, sizeof o);
+                    o.kind = OP_DVEC;
+                    o.pos = mask;
+                    o.ctl = o.ctl2 = -1;
+                    o.slot = -1;
+                    p->ops.push_back(o);
+                    wait.vecs.push_back({(int)p->ops.size() - 1, f});
+                    sign_op = -1;
+                }
+                for (int vi : hoisted) {
+                    sign_op = -1;
+                    core_grads(units[vi]);
+                    done_grad[vi] = 1;
+                }
+            };
+            for (size_t at = 0; at < grp.second.size(); ++at) {
+                const int ui = grp.second[at];
                 const Unit& U = units[ui];
                 if (backward) order.insert(order.end(), U.gates.rbegin(), U.gates.rend());
                 else order.insert(order.end(), U.gates.begin(), U.gates.end());
@@ -730,6 +1094,61 @@ struct PassBuilder {
                     }
                     continue;
                 }
+                if (cores && !is_multi(G.kind) && U.core == CORE_NONE) {
+                    // diagonal run: one component serves all its angles; the phases wait
+                    // for the next multiplication if the qubit is (still) to be in
+                    // registers, else they are applied by index bit here
+                    int slot = -1;
+                    for (int j = (int)U.gates.size() - 1; j >= 0; --j) {
+                        if (p->gates[U.gates[j]].src == QSV_SRC_NONE) continue;
+                        if (slot < 0) {
+                            sign_op = -1;
+                            slot = comp(U, OP_GZ, -1, -1);
+                        }
+                        gout(U.gates[j], -1, slot, -1, -1, 0);
+                    }
+                    if (starts_timelines()) {
+                        wait.diag[U.qubit].clear();
+                        continue;
+                    }
+                    if (last_in_regs[U.qubit] >= gi) {
+                        wait.diag[U.qubit].push_back({F_DIAG, 0, CORE_NONE, true, U.gates});
+                        continue;
+                    }
+                }
+                if (cores && U.core != CORE_NONE) {
+                    const bool skip = starts_timelines();
+                    if (!wait.diag[U.qubit].empty() || (!done_pre[ui] && !pre_factors(U).empty())) flush(at);
+                    if (!done_grad[ui]) {
+                        sign_op = -1;
+                        core_grads(U);
+                    }
+                    if (skip) continue;
+                    DOp o;
+                    std::memset(&o, 0, sizeof o);
+                    const std::vector<int> core = sub_gates(U, U.lead, U.tail);
+                    o.pos = pos_of(U.qubit);
+                    o.sh = W - 1 - U.qubit;
+                    o.ctl = o.ctl2 = -1;
+                    o.slot = -1;
+                    if (U.core == CORE_FIXED) {
+                        o.kind = recipe_class(p, core);
+                        o.mat = add_recipe(p, core, true);
+                    } else {
+                        o.kind = U.core == CORE_RX ? OP_SHX : OP_SHY;
+                        o.mat = add_shear(p, core, U.core, true);
+                    }
+                    sign_op = -1;
+                    p->ops.push_back(o);
+                    if (U.core == CORE_GEN) wait.diag[U.qubit].push_back({F_PRE, 0, U.core, true, core});
+                    continue;
+                }
+                if (cores)  // a controlled gate acts densely on its target: nothing may wait there
+                    for (int q = 0; q < W; ++q)
+                        if ((U.D >> q & 1) && !wait.diag[q].empty()) {
+                            flush(at);
+                            break;
+                        }
                 sign_op = -1;
                 auto comp_op = [&](int kind) {
                     DOp o;
@@ -769,7 +1188,7 @@ struct PassBuilder {
                         }
                         p->gouts.push_back(go);
                     }
-                } else if (backward) {
+                } else if (backward && !(cores && !is_multi(G.kind))) {
                     // gradient partial (before uncomputing the gate), then U^dagger
                     const int g = U.gates[0];
                     if (G.src != QSV_SRC_NONE) {
@@ -812,9 +1231,20 @@ struct PassBuilder {
                 }
                 p->ops.push_back(o);
             }
+            if (cores) {
+                // phases of qubits that no later stage of the pass holds in registers
+                for (int r = 0; r < kRegBits; ++r) {
+                    const int q = W - 1 - ps.lq[st.reg[r]];
+                    if (last_in_regs[q] == gi && !wait.diag[q].empty()) {
+                        flush(grp.second.size());
+                        break;
+                    }
+                }
+            }
             st.op1 = (int32_t)p->ops.size();
             p->stages.push_back(st);
         }
+        for (auto& v : wait.vecs) p->ops[v.op].mat = add_factors(p, v.f);
         ps.n_gslots = nslot;
         ps.n_gout = (int32_t)p->gouts.size() - ps.gout0;
         out.push_back(ps);
@@ -831,6 +1261,8 @@ double op_flops(const DOp& o) {
     case OP_DIAG: return 6.0 * half;
     case OP_GX: case OP_GY: return 3.5 * half;
     case OP_GZ: return 4.0 * half;
+    case OP_SHY: case OP_SHX: return 6.0;  // three multiply-adds per amplitude
+    case OP_DVEC: return 6.0 * (1.0 - 1.0 / (double)(1 << popc((uint32_t)o.pos)));
     default: return 0.0;               // sign flips and swaps move data only
     }
 }
@@ -840,7 +1272,7 @@ double pass_flops(const qsv_plan_t* p, const DPass& ps, bool backward) {
     for (int s = ps.stage0; s < ps.stage0 + ps.n_stages; ++s)
         for (int o = p->stages[s].op0; o < p->stages[s].op1; ++o) {
             const DOp& op = p->ops[o];
-            const bool grad = op.kind >= OP_GX;
+            const bool grad = is_grad_op(op.kind);
             f += op_flops(op) * (backward && !grad ? 2.0 : 1.0);
         }
     return f;
@@ -888,9 +1320,33 @@ int pg_class(const qsv_plan_t* p, int g) {
     return recipe_class(p, std::vector<int>{g});
 }
 
+// Recipes in the order k_coef takes them: shared ones first, then the
+// per-sample ones, and in each the single values before the 16-entry vectors.
+void sort_recipes(qsv_plan_t* p) {
+    const auto cls = [](const DRecipe& r) { return 4 * r.dir + (r.out < 0 ? 2 : 0) + (r.kind == RC_DVEC ? 1 : 0); };
+    std::stable_sort(p->recipes.begin(), p->recipes.end(),
+                     [&](const DRecipe& a, const DRecipe& b) { return cls(a) < cls(b); });
+    std::memset(p->n_recipe_cls, 0, sizeof p->n_recipe_cls);
+    for (const DRecipe& r : p->recipes) p->n_recipe_cls[cls(r) / 4][cls(r) % 4]++;
+}
+
+int build_schedule(qsv_plan_t* p);
+
 }  // namespace
 
 int build_plan(qsv_plan_t* p) {
+    const int rc = build_schedule(p);
+    if (rc != QSV_OK) return rc;
+    sort_recipes(p);
+    if (p->opts.method == QSV_METHOD_PER_GATE) {
+        p->ref_shared = p->n_shared_mats[0] + p->n_shared_mats[1];
+        p->ref_ps = p->n_ps_mats[0] + p->n_ps_mats[1];
+    }
+    return QSV_OK;
+}
+
+namespace {
+int build_schedule(qsv_plan_t* p) {
     const int W = p->W;
     const qsv_opts& o = p->opts;
     // gate cache
@@ -940,7 +1396,10 @@ int build_plan(qsv_plan_t* p) {
         }
     }
     p->prefix_mat.resize(W);
-    for (int q = 0; q < W; ++q) p->prefix_mat[q] = add_recipe(p, pre[q], false);
+    for (int q = 0; q < W; ++q) {
+        p->prefix_mat[q] = add_recipe(p, pre[q], false);
+        ++(p->prefix_mat[q] < 0 ? p->ref_ps : p->ref_shared);
+    }
     std::vector<int> body, all;
     for (int g = 0; g < p->n_gates; ++g) {
         all.push_back(g);
@@ -968,6 +1427,7 @@ int build_plan(qsv_plan_t* p) {
             p->pg_fwd.push_back(x);
             p->fwd_order.push_back(g);
         }
+        p->dir = 1;
         for (int g = p->n_gates - 1; g >= 0; --g) {
             PGate x;
             std::memset(&x, 0, sizeof x);
@@ -1020,6 +1480,7 @@ int build_plan(qsv_plan_t* p) {
         std::vector<uint32_t> dense;
         auto passes = pack_passes(p, p->blocks, m, c, max_grads, dense);
         if (!covers(passes, (size_t)p->n_gates)) return QSV_ERR_GATE;
+        p->dir = 1;
         PassBuilder pb{p, true, std::vector<int>(W, p->n_gates)};
         for (int g = p->n_gates - 1; g >= 0; --g) {
             const qsv_gate& G = p->gates[g];
@@ -1045,6 +1506,7 @@ int build_plan(qsv_plan_t* p) {
     set_partial_layout(p, int64_t(1) << (W - m));
     return QSV_OK;
 }
+}  // namespace
 
 // Many circuits in one plan: each circuit is planned on its own (fused,
 // table-driven kernels), then the tables are concatenated with every index
@@ -1088,8 +1550,9 @@ int build_multi(qsv_plan_t* p, const std::vector<CircuitIn>& cs) {
         const int g0 = (int)p->dgates.size(), rg0 = (int)p->recipe_gates.size();
         const int st0 = (int)p->stages.size(), op0 = (int)p->ops.size(), t0 = (int)p->terms.size();
         const int go0 = (int)p->gouts.size();
-        const int sh0 = p->n_shared_mats, ps0 = p->n_ps_mats;
-        auto fix_mat = [&](int32_t mat) { return mat >= 0 ? mat + sh0 : -((-mat - 1) + ps0) - 1; };
+        const int sh0[2] = {p->n_shared_mats[0], p->n_shared_mats[1]}, ps0[2] = {p->n_ps_mats[0], p->n_ps_mats[1]};
+        auto fix_mat = [&](int32_t mat, int dir) { return mat >= 0 ? mat + sh0[dir] : -((-mat - 1) + ps0[dir]) - 1; };
+        const int bwd_op0 = sub.bwd_pass.empty() ? (int)sub.ops.size() : sub.stages[sub.bwd_pass[0].stage0].op0;
         for (DGate g : sub.dgates) {
             if (g.src == QSV_SRC_WEIGHT) g.idx += w0;
             if (g.src == QSV_SRC_INPUT) g.idx += x0;
@@ -1098,26 +1561,31 @@ int build_multi(qsv_plan_t* p, const std::vector<CircuitIn>& cs) {
         for (int32_t g : sub.recipe_gates) p->recipe_gates.push_back(g + g0);
         for (DRecipe r : sub.recipes) {
             r.first += rg0;
-            r.out = fix_mat(r.out);
+            r.out = fix_mat(r.out, r.dir);
             p->recipes.push_back(r);
         }
-        p->n_shared_mats += sub.n_shared_mats;
-        p->n_ps_mats += sub.n_ps_mats;
-        for (int32_t m : sub.prefix_mat) p->prefix_mat.push_back(fix_mat(m));
+        for (int d2 = 0; d2 < 2; ++d2) {
+            p->n_shared_mats[d2] += sub.n_shared_mats[d2];
+            p->n_ps_mats[d2] += sub.n_ps_mats[d2];
+        }
+        p->ref_shared += sub.ref_shared;
+        p->ref_ps += sub.ref_ps;
+        for (int32_t m : sub.prefix_mat) p->prefix_mat.push_back(fix_mat(m, 0));
         for (DStage st : sub.stages) {
             st.op0 += op0;
             st.op1 += op0;
             p->stages.push_back(st);
         }
-        for (DOp o : sub.ops) {
-            if (o.kind != OP_SIGN && o.kind != OP_SWAP && o.kind < OP_GX) o.mat = fix_mat(o.mat);
+        for (int oi = 0; oi < (int)sub.ops.size(); ++oi) {
+            DOp o = sub.ops[oi];
+            if (o.kind != OP_SIGN && o.kind != OP_SWAP && !is_grad_op(o.kind)) o.mat = fix_mat(o.mat, oi >= bwd_op0);
             if (o.kind == OP_SIGN) o.term0 += t0;
             p->ops.push_back(o);
         }
         p->terms.insert(p->terms.end(), sub.terms.begin(), sub.terms.end());
         for (DGOut o : sub.gouts) {
             o.ord += ord0;
-            if (o.axis >= 0) o.mat = fix_mat(o.mat);
+            if (o.axis >= 0) o.mat = fix_mat(o.mat, 1);
             p->gouts.push_back(o);
         }
         for (DPass ps : sub.fwd_pass) {
@@ -1193,6 +1661,7 @@ int build_multi(qsv_plan_t* p, const std::vector<CircuitIn>& cs) {
     p->grad_csr[w0 + 1 + x0] = at;
     for (auto& l : wl) p->grad_csr.insert(p->grad_csr.end(), l.begin(), l.end());
     for (auto& l : xl) p->grad_csr.insert(p->grad_csr.end(), l.begin(), l.end());
+    sort_recipes(p);
     return QSV_OK;
 }
 

@@ -177,60 +177,240 @@ __device__ __forceinline__ int64_t insert_bit(int64_t x, int s, int v) {
     return ((x >> s) << (s + 1)) | (int64_t(v) << s) | lo;
 }
 
+// Launch shape of a one-dimensional grid of n_blocks blocks. HIP bounds the
+// threads of each grid dimension by 2^32, which the whole-batch kernels reach
+// from 2^32 amplitudes (32 GiB of complex64), so blocks beyond 2^16 spill into y.
+// Kernels launched this way read their block number from block_1d().
+static dim3 grid_1d(int64_t n_blocks) {
+    n_blocks = std::max<int64_t>(n_blocks, 1);  // every kernel launched this way bounds-checks its items
+    const int64_t gx = std::min<int64_t>(n_blocks, int64_t(1) << 16);
+    return dim3((unsigned)gx, (unsigned)((n_blocks + gx - 1) / gx));
+}
+__device__ __forceinline__ int64_t block_1d() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // ----------------------------------------------------------------------------
 // gate-matrix cache evaluation
 // ----------------------------------------------------------------------------
-template <class R>  // R: matrix entry type (float, or double for complex128 states)
-__global__ void k_coef(const DGate* __restrict__ gates, const DRecipe* __restrict__ recipes,
-                       const int32_t* __restrict__ rg, int n_recipes,
-                       const float* __restrict__ weights, const float* __restrict__ inputs,
-                       int n_inputs, int n_shared, int n_ps, int remap, R* __restrict__ mats) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = blockIdx.y;
-    if (r >= n_recipes) return;
-    const DRecipe Rc = recipes[r];
-    if (Rc.out >= 0 && b != 0) return;
-    double M[8] = {1, 0, 0, 0, 0, 0, 1, 0};
-    for (int i = 0; i < Rc.count; ++i) {
-        const DGate& G = gates[rg[Rc.first + i]];
-        double th = 0.0;
-        if (G.src == QSV_SRC_WEIGHT) {
-            th = (double)weights[G.idx];
-            if (remap) th = M_PI * tanh(th);  // weight remapping into (-pi, pi)
-        }
-        else if (G.src == QSV_SRC_INPUT) th = (double)inputs[(size_t)b * n_inputs + G.idx];
-        double s, c;
-        sincos(0.5 * th, &s, &c);
-        double g[8];
-        for (int e = 0; e < 8; ++e) g[e] = G.C[e] + c * G.A[e] + s * G.S[e];
-        // M <- g * M (later gates act on the left)
-        double N[8];
-        for (int row = 0; row < 2; ++row)
-            for (int col = 0; col < 2; ++col) {
-                double re = 0, im = 0;
-                for (int k = 0; k < 2; ++k) {
-                    const double ar = g[(row * 2 + k) * 2], ai = g[(row * 2 + k) * 2 + 1];
-                    const double br = M[(k * 2 + col) * 2], bi = M[(k * 2 + col) * 2 + 1];
-                    re += ar * br - ai * bi;
-                    im += ar * bi + ai * br;
-                }
-                N[(row * 2 + col) * 2] = re;
-                N[(row * 2 + col) * 2 + 1] = im;
+struct CoefIn {
+    const DGate* gates;
+    const int32_t* rg;
+    const float* weights;
+    const float* inputs;
+    int n_inputs, remap;
+};
+
+// v of lane J of this lane's quad
+template <int J>
+__device__ __forceinline__ double quad_lane(double v) {
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)x, J * 0x55, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), J * 0x55, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// M <- G * M for the gate matrix G held by lane J of the quad
+template <int J>
+__device__ __forceinline__ void coef_step(const double (&G)[8], double (&M)[8]) {
+    double g[8], N[8];
+    for (int e = 0; e < 8; ++e) g[e] = quad_lane<J>(G[e]);
+    for (int row = 0; row < 2; ++row)
+        for (int col = 0; col < 2; ++col) {
+            double re = 0, im = 0;
+            for (int k = 0; k < 2; ++k) {
+                const double ar = g[(row * 2 + k) * 2], ai = g[(row * 2 + k) * 2 + 1];
+                const double br = M[(k * 2 + col) * 2], bi = M[(k * 2 + col) * 2 + 1];
+                re += ar * br - ai * bi;
+                im += ar * bi + ai * br;
             }
-        for (int e = 0; e < 8; ++e) M[e] = N[e];
+            N[(row * 2 + col) * 2] = re;
+            N[(row * 2 + col) * 2 + 1] = im;
+        }
+    for (int e = 0; e < 8; ++e) M[e] = N[e];
+}
+
+// M <- the ordered product of `count` gates (recipe_gates[first ..]) at sample b,
+// evaluated by a quad of lanes: each takes one gate's matrix, then all four
+// form the product (later gates act on the left). n: the wave's largest count.
+__device__ __forceinline__ void coef_product(const CoefIn& in, int first, int count, int n, int b, double (&M)[8]) {
+    const int q = threadIdx.x & 3;
+    for (int e = 0; e < 8; ++e) M[e] = e == 0 || e == 6 ? 1.0 : 0.0;
+    for (int i0 = 0; i0 < n; i0 += 4) {
+        double G[8];
+        for (int e = 0; e < 8; ++e) G[e] = e == 0 || e == 6 ? 1.0 : 0.0;
+        if (i0 + q < count) {
+            const DGate& D = in.gates[in.rg[first + i0 + q]];
+            double th = 0.0;
+            if (D.src == QSV_SRC_WEIGHT) {
+                th = (double)in.weights[D.idx];
+                if (in.remap) th = M_PI * tanh(th);  // weight remapping into (-pi, pi)
+            } else if (D.src == QSV_SRC_INPUT) {
+                th = (double)in.inputs[(size_t)b * in.n_inputs + D.idx];
+            }
+            double s, c;
+            sincos(0.5 * th, &s, &c);
+            for (int e = 0; e < 8; ++e) G[e] = D.C[e] + c * D.A[e] + s * D.S[e];
+        }
+        coef_step<0>(G, M);
+        if (n > i0 + 1) coef_step<1>(G, M);
+        if (n > i0 + 2) coef_step<2>(G, M);
+        if (n > i0 + 3) coef_step<3>(G, M);
     }
-    R out[8];
-    if (Rc.dagger) {
-        out[0] = (R)M[0]; out[1] = (R)-M[1];  // m00*
-        out[2] = (R)M[4]; out[3] = (R)-M[5];  // m10*
-        out[4] = (R)M[2]; out[5] = (R)-M[3];  // m01*
-        out[6] = (R)M[6]; out[7] = (R)-M[7];  // m11*
+}
+
+// A rotation core U = M taken apart: U = +-diag(p0, p1) R(phi) diag(1, q1),
+// |phi| <= pi/2 (a = tan(phi/2), b = sin(phi)).
+struct CoreParts {
+    double2 p0, p1, q1;
+    double a, b;
+};
+__device__ __forceinline__ CoreParts coef_core(const double (&M)[8], int core) {
+    CoreParts o;
+    o.p0 = o.p1 = o.q1 = make_double2(1.0, 0.0);
+    double c, s;
+    if (core != CORE_GEN) {
+        c = M[0];
+        s = core == CORE_RX ? -M[5] : M[4];
     } else {
-        for (int e = 0; e < 8; ++e) out[e] = (R)M[e];
+        const double2 a = make_double2(M[0], M[1]), d = make_double2(M[4], M[5]);
+        c = sqrt(a.x * a.x + a.y * a.y);
+        s = sqrt(d.x * d.x + d.y * d.y);
+        // below 1e-10 an entry's phase cannot matter in float32
+        if (c > 1e-10 || !(c == c)) o.p0 = make_double2(a.x / c, a.y / c);
+        if (s > 1e-10 || !(s == s)) o.p1 = make_double2(d.x / s, d.y / s);
+        // q1 = det U / (p0 p1), which makes p0 q1 (-s) and p1 q1 c the other two entries
+        const double2 det = make_double2(M[0] * M[6] - M[1] * M[7] - (M[2] * M[4] - M[3] * M[5]),
+                                         M[0] * M[7] + M[1] * M[6] - (M[2] * M[5] + M[3] * M[4]));
+        const double2 pp = cmul(o.p0, o.p1);
+        const double2 q = cmul(det, make_double2(pp.x, -pp.y));
+        const double n = sqrt(q.x * q.x + q.y * q.y);
+        o.q1 = make_double2(q.x / n, q.y / n);
     }
+    if (c < 0.0) c = -c, s = -s;
+    o.a = s / (1.0 + c);
+    o.b = s;
+    return o;
+}
+
+__device__ __forceinline__ int wave_max(int v) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) v = max(v, __shfl_xor(v, o, 64));
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// Values of a plan's recipes for one call (see RecipeKind). A wave takes 16
+// single-value recipes, one per quad of lanes, or one 16-entry vector, whose
+// factors its quads evaluate side by side. n1 / n2 single values and vectors
+// are shared by the batch, p1 / p2 are per sample. A chain of dependent
+// loads, one sine and cosine and a few products bounds it, so every angle of a
+// list has a lane of its own (one thread per recipe, gate after gate, takes 3-8
+// times as long for the vectors). P, Q and phi of one core are evaluated by
+// different waves: by the same instructions, so that where an entry of U is
+// rounding noise its phase still comes out the same everywhere.
+template <class R>  // R: matrix entry type (float, or double for complex128 states)
+__global__ __launch_bounds__(64) void k_coef(CoefIn in, const DRecipe* __restrict__ recipes,
+                                             const DFactor* __restrict__ factors, int n1, int n2, int p1, int p2,
+                                             int B, int n_shared, int n_ps, R* __restrict__ mats) {
+    __shared__ double2 fac[16];
+    __shared__ int fpos[16];
+    const int lane = threadIdx.x, quad = lane >> 2;
+    int64_t g = block_1d();
+    const int gs = (n1 + 15) / 16, gp = (p1 + 15) / 16;
+    int first = 0, b = 0, k, lim = n1;
+    if (g < gs + n2) {
+        k = (int)g - gs;
+    } else {
+        g -= gs + n2;
+        if (gp + p2 == 0) return;
+        b = (int)(g / (gp + p2));
+        if (b >= B) return;
+        k = (int)(g % (gp + p2));
+        first = n1 + n2;
+        lim = p1;
+        g = k;
+        k -= gp;
+    }
+    const bool vec = k >= 0;  // the same for the whole wave
+    const int r = vec ? lim + k : (int)g * 16 + quad;
+    const bool on = vec || r < lim;
+    DRecipe Rc{};
+    if (on) Rc = recipes[first + r];
     R* dst = Rc.out >= 0 ? mats + 8 * (size_t)Rc.out
                          : mats + 8 * ((size_t)n_shared + (size_t)b * n_ps + (size_t)(-Rc.out - 1));
-    for (int e = 0; e < 8; ++e) dst[e] = out[e];
+    double2 D = make_double2(1.0, 0.0);
+    const int chunks = vec ? (Rc.count + 15) / 16 : 1;
+    for (int ch = 0; ch < chunks; ++ch) {
+        // this quad's gate list (the core's, for a RC_VMAT, whose product comes second)
+        int first1 = Rc.first, count1 = Rc.count, core = Rc.core;
+        DFactor F{};
+        if (vec) {
+            if (ch * 16 + quad < Rc.count) F = factors[Rc.first + ch * 16 + quad];
+            first1 = F.first;
+            count1 = F.count;
+            core = F.core;
+        } else if (Rc.kind == RC_VMAT) {
+            first1 = Rc.first2;
+            count1 = Rc.count2;
+        }
+        double A[8], C[8];
+        coef_product(in, first1, count1, wave_max(count1), b, C);
+        const CoreParts P = coef_core(C, core);
+        if (vec) {
+            double2 f0 = make_double2(1.0, 0.0), f1 = f0;
+            if (F.kind == F_DIAG) {
+                f0 = make_double2(C[0], C[1]);
+                f1 = make_double2(C[6], C[7]);
+            } else if (F.kind == F_POST) {
+                f0 = P.p0;
+                f1 = P.p1;
+            } else {
+                f1 = P.q1;
+            }
+            f1 = cmul(f1, make_double2(f0.x, -f0.y));
+            if (F.dagger) f1.y = -f1.y;
+            if ((lane & 3) == 0) {
+                fac[quad] = f1;
+                fpos[quad] = F.pos;
+            }
+            __syncthreads();
+            const int n = min(16, Rc.count - ch * 16);
+            for (int j = 0; j < n; ++j)
+                if ((lane >> fpos[j]) & 1) D = cmul(D, fac[j]);
+            __syncthreads();
+            continue;
+        }
+        const bool vmat = Rc.kind == RC_VMAT;
+        coef_product(in, Rc.first, vmat ? Rc.count : 0, wave_max(vmat ? Rc.count : 0), b, A);
+        if (!on || (lane & 3)) return;
+        if (Rc.kind == RC_SHEAR) {
+            dst[0] = (R)(Rc.dagger ? -P.a : P.a);  // R(phi)^dagger = R(-phi)
+            dst[1] = (R)(Rc.dagger ? -P.b : P.b);
+            return;
+        }
+        if (vmat) {
+            for (int col = 0; col < 2; ++col) {
+                const double2 u = cmul(make_double2(P.p0.x, -P.p0.y), make_double2(A[2 * col], A[2 * col + 1]));
+                const double2 v = cmul(make_double2(P.p1.x, -P.p1.y), make_double2(A[4 + 2 * col], A[5 + 2 * col]));
+                A[2 * col] = u.x;
+                A[2 * col + 1] = u.y;
+                A[4 + 2 * col] = v.x;
+                A[5 + 2 * col] = v.y;
+            }
+        } else {
+            for (int e = 0; e < 8; ++e) A[e] = C[e];
+        }
+        if (Rc.dagger) {
+            dst[0] = (R)A[0]; dst[1] = (R)-A[1];  // m00*
+            dst[2] = (R)A[4]; dst[3] = (R)-A[5];  // m10*
+            dst[4] = (R)A[2]; dst[5] = (R)-A[3];  // m01*
+            dst[6] = (R)A[6]; dst[7] = (R)-A[7];  // m11*
+        } else {
+            for (int e = 0; e < 8; ++e) dst[e] = (R)A[e];
+        }
+    }
+    if (vec && lane < 16) {
+        dst[2 * lane] = (R)D.x;
+        dst[2 * lane + 1] = (R)D.y;
+    }
 }
 
 // ----------------------------------------------------------------------------
@@ -414,17 +594,6 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ 
 // plain method (one sweep per gate)
 // ----------------------------------------------------------------------------
 constexpr int kPgItems = 4;
-
-// Launch shape of a one-dimensional grid of n_blocks blocks. HIP bounds the
-// threads of each grid dimension by 2^32, which the whole-batch kernels reach
-// from 2^32 amplitudes (32 GiB of complex64), so blocks beyond 2^16 spill into y.
-// Kernels launched this way read their block number from block_1d().
-static dim3 grid_1d(int64_t n_blocks) {
-    n_blocks = std::max<int64_t>(n_blocks, 1);  // every kernel launched this way bounds-checks its items
-    const int64_t gx = std::min<int64_t>(n_blocks, int64_t(1) << 16);
-    return dim3((unsigned)gx, (unsigned)((n_blocks + gx - 1) / gx));
-}
-__device__ __forceinline__ int64_t block_1d() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 
 template <class V>
 __device__ __forceinline__ void pair_apply(int cls, const M2T<V>& M, V& x, V& y) {
@@ -1806,12 +1975,12 @@ int get_tables(const qsv_plan_t* p, DeviceTables** out) {
                             bytes_of(p->fwd_pass), bytes_of(p->bwd_pass), bytes_of(p->stages),
                             bytes_of(p->ops), bytes_of(p->terms), bytes_of(p->gouts),
                             bytes_of(p->prefix_mat), bytes_of(p->grad_csr), bytes_of(p->pu),
-                            bytes_of(p->nchv), bytes_of(p->circ)};
+                            bytes_of(p->nchv), bytes_of(p->circ), bytes_of(p->factors)};
     const void* srcs[] = {p->dgates.data(), p->recipes.data(), p->recipe_gates.data(),
                           p->fwd_pass.data(), p->bwd_pass.data(), p->stages.data(),
                           p->ops.data(), p->terms.data(), p->gouts.data(),
                           p->prefix_mat.data(), p->grad_csr.data(), p->pu.data(), p->nchv.data(),
-                          p->circ.data()};
+                          p->circ.data(), p->factors.data()};
     const int n = (int)(sizeof(sizes) / sizeof(sizes[0]));
     size_t total = 0, offs[16];
     for (int i = 0; i < n; ++i) { offs[i] = total; total += align256(std::max<size_t>(sizes[i], 1)); }
@@ -1849,6 +2018,7 @@ int get_tables(const qsv_plan_t* p, DeviceTables** out) {
     t.pu = (int64_t*)(c + offs[11]);
     t.nchv = (int32_t*)(c + offs[12]);
     t.circ = (DCirc*)(c + offs[13]);
+    t.factors = (DFactor*)(c + offs[14]);
     if (p->opts.method == QSV_METHOD_FUSED && p->opts.codegen && !p->multi &&
         !(p->fwd_pass.empty() && p->bwd_pass.empty())) {
         JitModules jm;
@@ -1894,7 +2064,16 @@ bool c128(const qsv_plan_t* p) { return p->opts.amp_dtype == QSV_AMP_C128; }
 size_t amp_size(const qsv_plan_t* p) { return c128(p) ? 16 : 8; }
 
 size_t mats_bytes(const qsv_plan_t* p, int64_t B) {
-    return align256(((size_t)p->n_shared_mats + (size_t)B * p->n_ps_mats) * 8 * (amp_size(p) / 2) + 32);
+    const int sh = std::max(std::max(p->n_shared_mats[0], p->n_shared_mats[1]), p->ref_shared);
+    const int ps = std::max(std::max(p->n_ps_mats[0], p->n_ps_mats[1]), p->ref_ps);
+    return align256(((size_t)sh + (size_t)B * ps) * 8 * (amp_size(p) / 2) + 32);
+}
+
+// The matrices of a forward alone, as the allocation-free call lays them out
+// (and counts them against its limit): ref_shared and ref_ps are never less
+// than the forward's own slots.
+size_t fwd_mats_bytes(const qsv_plan_t* p, int64_t B) {
+    return align256(((size_t)p->ref_shared + (size_t)B * p->ref_ps) * 8 * (amp_size(p) / 2) + 32);
 }
 
 int64_t grad_nch(const qsv_plan_t* p) {
@@ -1950,20 +2129,23 @@ int check_plan(const qsv_plan_t* p) {
     return QSV_OK;
 }
 
-int run_coef(const qsv_plan_t* p, DeviceTables* T, const float* w, const float* x, int64_t B,
+int run_coef(const qsv_plan_t* p, DeviceTables* T, int dir, const float* w, const float* x, int64_t B,
              float* mats, hipStream_t s) {
-    const int nr = (int)p->recipes.size();
-    if (nr == 0) return QSV_OK;
-    dim3 grid((nr + 127) / 128, (unsigned)(p->n_ps_mats ? B : 1));
+    const int* n = p->n_recipe_cls[dir];
+    if (n[0] + n[1] + n[2] + n[3] == 0) return QSV_OK;
+    const int nsh = p->n_shared_mats[dir], nps = p->n_ps_mats[dir];
+    const DRecipe* rec = T->recipes;
+    for (int i = 0; i < 4; ++i) rec += dir ? p->n_recipe_cls[0][i] : 0;
+    const int64_t waves = (n[0] + 15) / 16 + n[1] + B * ((n[2] + 15) / 16 + n[3]);
+    const CoefIn in = {T->gates, T->recipe_gates, w, x, p->n_inputs, (int)p->opts.weight_remap};
     hipEvent_t ev = prof_begin(p, s);
     if (c128(p))
-        hipLaunchKernelGGL(k_coef<double>, grid, dim3(128), 0, s, T->gates, T->recipes, T->recipe_gates, nr,
-                           w, x, p->n_inputs, p->n_shared_mats, p->n_ps_mats, (int)p->opts.weight_remap,
-                           (double*)mats);
+        hipLaunchKernelGGL(k_coef<double>, grid_1d(waves), dim3(64), 0, s, in, rec, T->factors,
+                           n[0], n[1], n[2], n[3], (int)B, nsh, nps, (double*)mats);
     else
-        hipLaunchKernelGGL(k_coef<float>, grid, dim3(128), 0, s, T->gates, T->recipes, T->recipe_gates, nr,
-                           w, x, p->n_inputs, p->n_shared_mats, p->n_ps_mats, (int)p->opts.weight_remap, mats);
-    prof_end(p, s, ev, K_COEF, 4.0 * (double)amp_size(p) * ((double)p->n_shared_mats + (double)B * p->n_ps_mats),
+        hipLaunchKernelGGL(k_coef<float>, grid_1d(waves), dim3(64), 0, s, in, rec, T->factors,
+                           n[0], n[1], n[2], n[3], (int)B, nsh, nps, mats);
+    prof_end(p, s, ev, K_COEF, 4.0 * (double)amp_size(p) * ((double)nsh + (double)B * nps),
              0.0);
     HIP_TRY(hipGetLastError());
     return QSV_OK;
@@ -1977,10 +2159,10 @@ int run_init(const qsv_plan_t* p, DeviceTables* T, const float* mats, int64_t B,
     const int vec = ((uintptr_t)st & 15) == 0;
     if (c128(p))
         hipLaunchKernelGGL(k_init<double2>, grid, dim3(256), 0, s, (double2*)st, p->W, T->prefix_mat,
-                           (const double*)mats, p->n_shared_mats, p->n_ps_mats, vec);
+                           (const double*)mats, p->n_shared_mats[0], p->n_ps_mats[0], vec);
     else
         hipLaunchKernelGGL(k_init<float2>, grid, dim3(256), 0, s, st, p->W, T->prefix_mat, mats,
-                           p->n_shared_mats, p->n_ps_mats, vec);
+                           p->n_shared_mats[0], p->n_ps_mats[0], vec);
     const double amps = (double)B * (double)(int64_t(1) << p->W);
     prof_end(p, s, ev, K_INIT, (double)amp_size(p) * amps, 0.0);
     HIP_TRY(hipGetLastError());
@@ -2396,6 +2578,8 @@ int qsv_plan_gate_blocks(const qsv_plan_t* p, int32_t* block_of_gate) {
     return QSV_OK;
 }
 
+static size_t readout_bytes(const qsv_plan_t* p, int64_t B);
+
 size_t qsv_workspace_size(const qsv_plan_t* p, int64_t B, int32_t op) {
     if (check_plan(p) || B <= 0) return 0;
     switch (op) {
@@ -2407,15 +2591,7 @@ size_t qsv_workspace_size(const qsv_plan_t* p, int64_t B, int32_t op) {
         return mats_bytes(p, B) + 2 * align256(state_bytes(p, B)) + kLamSkew + partial_bytes(p, B);
     case QSV_OP_STEP:
         return std::max(qsv_workspace_size(p, B, QSV_OP_BACKWARD), qsv_workspace_size(p, B, QSV_OP_FORWARD_EXPVAL));
-    case QSV_OP_FORWARD_EXPVAL: {
-        // forward matrices, then readout partials: per generated tile (fused
-        // readout) or per readout chunk, whichever is more
-        size_t part = qsv_workspace_size(p, B, QSV_OP_EXPVAL);
-        if (!p->multi)
-            part = std::max(part, align256((size_t)B * ((size_t)1 << (p->W - std::min(p->opts.tile_qubits, p->W))) *
-                                           p->W * sizeof(double)));
-        return mats_bytes(p, B) + part;
-    }
+    case QSV_OP_FORWARD_EXPVAL: return mats_bytes(p, B) + readout_bytes(p, B);
     default: return 0;
     }
 }
@@ -2433,7 +2609,7 @@ static int forward_impl(const qsv_plan_t* p, const float* w, const float* x, int
     int rc;
     float* mats = (float*)ws;
     float2* st = (float2*)d_state;
-    if ((rc = run_coef(p, T, w, x, B, mats, s))) return rc;
+    if ((rc = run_coef(p, T, 0, w, x, B, mats, s))) return rc;
     if (p->multi) {
         DeviceTables::Queue* Q;
         if ((rc = get_queue(p, T, B, &Q))) return rc;
@@ -2448,7 +2624,7 @@ static int forward_impl(const qsv_plan_t* p, const float* w, const float* x, int
             ev = prof_begin(p, s);
             hipLaunchKernelGGL(k_init_multi, dim3((unsigned)p->nchunk_tot, (unsigned)B), dim3(256), 0, s,
                                (const DCirc*)T->circ, (int)p->circ.size(), st, p->row, T->prefix_mat,
-                               (const float*)mats, p->n_shared_mats, p->n_ps_mats);
+                               (const float*)mats, p->n_shared_mats[0], p->n_ps_mats[0]);
             prof_end(p, s, ev, K_INIT, 8.0 * amps, 0.0);
         }
         double flops = 0.0, bytes = 0.0;
@@ -2464,7 +2640,7 @@ static int forward_impl(const qsv_plan_t* p, const float* w, const float* x, int
             hipLaunchKernelGGL(k_multi_fwd, dim3((unsigned)n), dim3(256), multi_lds(p), s,
                                (const DCirc*)T->circ, (const DItem*)(Q->fwd + i0), (const DPass*)T->fwd_pass,
                                (const DStage*)T->stages, (const DOp*)T->ops, (const DTerm*)T->terms,
-                               (const float*)mats, p->n_shared_mats, p->n_ps_mats, T->prefix_mat, st, p->row);
+                               (const float*)mats, p->n_shared_mats[0], p->n_ps_mats[0], T->prefix_mat, st, p->row);
         }
         prof_end(p, s, ev, K_MULTI_FWD, bytes, flops);
         HIP_TRY(hipGetLastError());
@@ -2493,14 +2669,14 @@ static int forward_impl(const qsv_plan_t* p, const float* w, const float* x, int
                 const int64_t vitems = (pg.cls == OP_DIAG || vmode == PG_VEC_SWEEP) ? (B << W) / 2
                                      : vmode == PG_VEC_ADJ ? (B << (W - nfix)) : (B << (W - nfix)) / 2;
                 hipLaunchKernelGGL(k_pg_apply_vec, grid_1d((vitems + 255) / 256), dim3(256), 0, s, st, W,
-                                   vitems, pg, vmode, (const float*)mats, p->n_shared_mats, p->n_ps_mats,
+                                   vitems, pg, vmode, (const float*)mats, p->n_shared_mats[0], p->n_ps_mats[0],
                                    pg_reverse(pg, vmode, i, (int64_t)state_bytes(p, B)));
             } else if (c128(p)) {
                 hipLaunchKernelGGL(k_pg_apply<double2>, grid_1d(blocks), dim3(256), 0, s, (double2*)st, W,
-                                   B, pg, (const double*)mats, p->n_shared_mats, p->n_ps_mats);
+                                   B, pg, (const double*)mats, p->n_shared_mats[0], p->n_ps_mats[0]);
             } else {
                 hipLaunchKernelGGL(k_pg_apply<float2>, grid_1d(blocks), dim3(256), 0, s, st, W, B, pg,
-                                   (const float*)mats, p->n_shared_mats, p->n_ps_mats);
+                                   (const float*)mats, p->n_shared_mats[0], p->n_ps_mats[0]);
             }
             prof_end(p, s, ev, K_PG_APPLY, 2.0 * (double)amp_size(p) * touched * amps, p->pg_fwd_flops[i] * amps,
                      kPgSub0 + pg_prof_class(pg));
@@ -2515,7 +2691,7 @@ static int forward_impl(const qsv_plan_t* p, const float* w, const float* x, int
     for (size_t i = 0; i < p->fwd_pass.size(); ++i) {
         hipEvent_t ev = prof_begin(p, s);
         if (!T->fwd_fn.empty()) {
-            int ns = p->n_shared_mats, np = p->n_ps_mats;
+            int ns = p->n_shared_mats[0], np = p->n_ps_mats[0];
             const float* mp = mats;
             double* ep = epart;
             void* args[] = {&st, &mp, &ns, &np, &ep};  // the last pass takes the readout pointer
@@ -2523,8 +2699,8 @@ static int forward_impl(const qsv_plan_t* p, const float* w, const float* x, int
                                           s, args, nullptr));
         } else {
             hipLaunchKernelGGL(k_pass_fwd, dim3(tiles), dim3(threads), lds, s, T->fwd_pass + i,
-                               T->stages, T->ops, T->terms, (const float*)mats, p->n_shared_mats,
-                               p->n_ps_mats, T->prefix_mat, st, W);
+                               T->stages, T->ops, T->terms, (const float*)mats, p->n_shared_mats[0],
+                               p->n_ps_mats[0], T->prefix_mat, st, W);
         }
         // a first pass that builds the initial state reads nothing; a last pass
         // with the readout adds its partials
@@ -2550,9 +2726,43 @@ int qsv_forward(const qsv_plan_t* p, const float* w, const float* x, int64_t B, 
     return forward_impl(p, w, x, B, d_state, ws, (hipStream_t)stream, T, nullptr);
 }
 
+// readout partials of a forward with readout: per generated tile (fused
+// readout) or per readout chunk, whichever is more
+static size_t readout_bytes(const qsv_plan_t* p, int64_t B) {
+    const size_t part = qsv_workspace_size(p, B, QSV_OP_EXPVAL);
+    if (p->multi) return part;
+    return std::max(part, align256((size_t)B * ((size_t)1 << (p->W - std::min(p->opts.tile_qubits, p->W))) * p->W *
+                                   sizeof(double)));
+}
+
+// qsv_forward_expval with its workspace split by the caller: matrices in ws,
+// readout partials behind the first mats_sz bytes
+static int forward_expval_impl(const qsv_plan_t* p, const float* w, const float* x, int64_t B, void* d_state,
+                               double* out, void* ws, size_t mats_sz, void* stream) {
+    TraceRange trace_("qsv_forward_expval");
+    int rc;
+    hipStream_t s = (hipStream_t)stream;
+    DeviceTables* T;
+    if ((rc = get_tables(p, &T))) return rc;
+    char* wsc = (char*)ws;
+    if (!fused_readout(p, T)) {
+        rc = forward_impl(p, w, x, B, d_state, ws, s, T, nullptr);
+        if (!rc) rc = qsv_expval(p, d_state, B, out, wsc + mats_sz, readout_bytes(p, B), stream);
+        return rc;
+    }
+    double* part = (double*)(wsc + mats_sz);
+    if ((rc = forward_impl(p, w, x, B, d_state, ws, s, T, part))) return rc;
+    const int64_t ntiles = int64_t(1) << (p->W - std::min(p->opts.tile_qubits, p->W));
+    hipEvent_t ev = prof_begin(p, s);
+    hipLaunchKernelGGL(k_expval_final, dim3((unsigned)p->W, (unsigned)B), dim3(256), 0, s, (const double*)part,
+                       p->W, ntiles, out);
+    prof_end(p, s, ev, K_EXPVAL_FINAL, 8.0 * (double)B * ntiles * p->W, 0.0);
+    HIP_TRY(hipGetLastError());
+    return QSV_OK;
+}
+
 int qsv_forward_expval(const qsv_plan_t* p, const float* w, const float* x, int64_t B, void* d_state,
                        double* out, void* ws, size_t ws_bytes, void* stream) {
-    TraceRange trace_("qsv_forward_expval");
     int rc = check_plan(p);
     if (rc) return rc;
     if ((rc = check_batch(p, B))) return rc;
@@ -2562,25 +2772,7 @@ int qsv_forward_expval(const qsv_plan_t* p, const float* w, const float* x, int6
     }
     const size_t need = qsv_workspace_size(p, B, QSV_OP_FORWARD_EXPVAL);
     if (!ws || ws_bytes < need) { set_error("forward_expval workspace too small"); return QSV_ERR_ARG; }
-    hipStream_t s = (hipStream_t)stream;
-    DeviceTables* T;
-    if ((rc = get_tables(p, &T))) return rc;
-    const size_t fwd_bytes = qsv_workspace_size(p, B, QSV_OP_FORWARD);
-    char* wsc = (char*)ws;
-    if (!fused_readout(p, T)) {
-        rc = forward_impl(p, w, x, B, d_state, ws, s, T, nullptr);
-        if (!rc) rc = qsv_expval(p, d_state, B, out, wsc + fwd_bytes, ws_bytes - fwd_bytes, stream);
-        return rc;
-    }
-    double* part = (double*)(wsc + fwd_bytes);
-    if ((rc = forward_impl(p, w, x, B, d_state, ws, s, T, part))) return rc;
-    const int64_t ntiles = int64_t(1) << (p->W - std::min(p->opts.tile_qubits, p->W));
-    hipEvent_t ev = prof_begin(p, s);
-    hipLaunchKernelGGL(k_expval_final, dim3((unsigned)p->W, (unsigned)B), dim3(256), 0, s, (const double*)part,
-                       p->W, ntiles, out);
-    prof_end(p, s, ev, K_EXPVAL_FINAL, 8.0 * (double)B * ntiles * p->W, 0.0);
-    HIP_TRY(hipGetLastError());
-    return QSV_OK;
+    return forward_expval_impl(p, w, x, B, d_state, out, ws, mats_bytes(p, B), stream);
 }
 
 // The workspace of qsv_forward_expval_noalloc: a file-scope device array,
@@ -2619,7 +2811,7 @@ int qsv_forward_expval_noalloc(const qsv_plan_t* p, const float* w, const float*
         set_error("null pointer");
         return QSV_ERR_ARG;
     }
-    const size_t need = qsv_workspace_size(p, B, QSV_OP_FORWARD_EXPVAL);
+    const size_t need = fwd_mats_bytes(p, B) + readout_bytes(p, B);
     if (need > (size_t)QSV_NOALLOC_SCRATCH_BYTES) {
         char buf[160];
         std::snprintf(buf, sizeof buf, "this plan and batch need %zu bytes of scratch, above the %zu-byte "
@@ -2632,7 +2824,7 @@ int qsv_forward_expval_noalloc(const qsv_plan_t* p, const float* w, const float*
     // the same launches as qsv_forward_expval on the scratch array; g_noalloc
     // turns every lazy creation (tables, kernels, work lists, events) into an error
     g_noalloc = true;
-    rc = qsv_forward_expval(p, w, x, B, d_state, out, ws, (size_t)QSV_NOALLOC_SCRATCH_BYTES, stream);
+    rc = forward_expval_impl(p, w, x, B, d_state, out, ws, fwd_mats_bytes(p, B), stream);
     g_noalloc = false;
     return rc;
 }
@@ -2711,7 +2903,7 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
     c += align256(state_bytes(p, B));
     double* part = (double*)c;
     c += partial_bytes(p, B);
-    if ((rc = run_coef(p, T, w, x, B, mats, s))) return rc;
+    if ((rc = run_coef(p, T, 1, w, x, B, mats, s))) return rc;
     const int64_t nch = grad_nch(p);
     const double amps = (double)B * (double)(int64_t(1) << W);
     if (p->multi) {
@@ -2731,8 +2923,8 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
             hipLaunchKernelGGL(k_multi_bwd, dim3((unsigned)n), dim3(256), multi_lds(p), s,
                                (const DCirc*)T->circ, (const DItem*)(Q->bwd + i0), (const DPass*)T->bwd_pass,
                                (const DStage*)T->stages, (const DOp*)T->ops, (const DTerm*)T->terms,
-                               (const DGOut*)T->gouts, (const float*)mats, p->n_shared_mats,
-                               p->n_ps_mats, (const float2*)d_state, psi, lam, gout, p->Wtot, p->row, (int)B,
+                               (const DGOut*)T->gouts, (const float*)mats, p->n_shared_mats[1],
+                               p->n_ps_mats[1], (const float2*)d_state, psi, lam, gout, p->Wtot, p->row, (int)B,
                                part, (const int64_t*)T->pu);
         }
         prof_end(p, s, ev, K_MULTI_BWD, bytes, flops);
@@ -2754,16 +2946,16 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
             const int vmode = pg_vec_mode(p, pg, psi);
             if (vmode != PG_SCALAR)
                 hipLaunchKernelGGL(k_pg_adj_vec, dim3((unsigned)nch, (unsigned)B), dim3(256), 0, s, psi, lam, W,
-                                   (int)B, pg, vmode, (const float*)mats, p->n_shared_mats, p->n_ps_mats, part,
+                                   (int)B, pg, vmode, (const float*)mats, p->n_shared_mats[1], p->n_ps_mats[1], part,
                                    nch, pg_reverse(pg, vmode, i, (int64_t)state_bytes(p, B)));
             else if (c128(p))
                 hipLaunchKernelGGL(k_pg_adj<double2>, dim3((unsigned)nch, (unsigned)B), dim3(256), 0, s,
                                    (double2*)psi, (double2*)lam, W, (int)B, pg, (const double*)mats,
-                                   p->n_shared_mats, p->n_ps_mats, part, nch);
+                                   p->n_shared_mats[1], p->n_ps_mats[1], part, nch);
             else
                 hipLaunchKernelGGL(k_pg_adj<float2>, dim3((unsigned)nch, (unsigned)B), dim3(256), 0, s, psi,
-                                   lam, W, (int)B, pg, (const float*)mats, p->n_shared_mats,
-                                   p->n_ps_mats, part, nch);
+                                   lam, W, (int)B, pg, (const float*)mats, p->n_shared_mats[1],
+                                   p->n_ps_mats[1], part, nch);
             prof_end(p, s, ev, K_PG_ADJ, 4.0 * (double)amp_size(p) * touched * amps, p->pg_bwd_flops[i] * amps,
                      kPgSub0 + pg_prof_class(pg));
         }
@@ -2780,14 +2972,14 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
             if (!T->bwd_fn.empty()) {
                 const void* psiN = d_state;
                 const float* mp = mats;
-                int ns = p->n_shared_mats, np = p->n_ps_mats, bb = (int)B;
+                int ns = p->n_shared_mats[1], np = p->n_ps_mats[1], bb = (int)B;
                 void* args[] = {&psiN, &psi, &lam, &gout, &mp, &ns, &np, &part, &bb};
                 HIP_TRY(hipModuleLaunchKernel((hipFunction_t)T->bwd_fn[i], tiles, 1, 1, threads, 1, 1, 0,
                                               s, args, nullptr));
             } else {
                 hipLaunchKernelGGL(k_pass_bwd, dim3(tiles), dim3(threads), lds, s, T->bwd_pass + i,
                                    T->stages, T->ops, T->terms, T->gouts, (const float*)mats,
-                                   p->n_shared_mats, p->n_ps_mats, (const float2*)d_state, psi, lam,
+                                   p->n_shared_mats[1], p->n_ps_mats[1], (const float2*)d_state, psi, lam,
                                    gout, W, (int)B, part, (const int64_t*)T->pu);
             }
             prof_end(p, s, ev, K_PASS_BWD, per_amp * amps, p->bwd_pass_flops[i] * amps,
