@@ -68,21 +68,44 @@ std::string scatter(const std::string& var, const std::vector<int>& pos) {
 
 int swz_host(int l) { return l ^ (((l >> 5) ^ (l >> 10)) & 31); }
 
+// Where a tile's local bits live: four in the register index, the others in
+// the thread index (the six lane bits first, then the wave bits).
 struct Layout {
     int reg[kRegBits];
-    std::vector<int> nonreg;  // local bits fed by the thread index, ascending
+    std::vector<int> nonreg;  // local bit of thread-index bit i
 };
 
-Layout make_layout(int m, const int* reg) {
+constexpr int kLaneBits = 6;
+
+// `wave`: mask of the local bits on the wave index; lane and wave bits ascend.
+Layout make_layout(int m, const int* reg, unsigned wave) {
     Layout L;
     for (int p = 0; p < kRegBits; ++p) L.reg[p] = reg[p];
-    for (int j = 0; j < m; ++j)
-        if (std::find(reg, reg + kRegBits, j) == reg + kRegBits) L.nonreg.push_back(j);
+    for (int w = 0; w < 2; ++w)
+        for (int j = 0; j < m; ++j)
+            if (std::find(reg, reg + kRegBits, j) == reg + kRegBits && (int)(wave >> j & 1) == w) L.nonreg.push_back(j);
     return L;
 }
 
+// mask of the top local bits outside `reg`, as many as there are wave bits
+unsigned top_wave_bits(int m, const int* reg) {
+    unsigned w = 0;
+    for (int j = m - 1, n = std::max(0, m - kRegBits - kLaneBits); n > 0; --j)
+        if (std::find(reg, reg + kRegBits, j) == reg + kRegBits) {
+            w |= 1u << j;
+            --n;
+        }
+    return w;
+}
+
+unsigned wave_bits(const Layout& L) {
+    unsigned w = 0;
+    for (size_t i = kLaneBits; i < L.nonreg.size(); ++i) w |= 1u << L.nonreg[i];
+    return w;
+}
+
 bool same(const Layout& a, const Layout& b) {
-    return std::equal(a.reg, a.reg + kRegBits, b.reg);
+    return std::equal(a.reg, a.reg + kRegBits, b.reg) && a.nonreg == b.nonreg;
 }
 
 class Gen {
@@ -94,6 +117,27 @@ public:
 typedef float2 f2;
 typedef float qsv_v4f __attribute__((ext_vector_type(4)));
 typedef __UINTPTR_TYPE__ qsv_uptr;  // pointer-sized integer without any header
+// Raw buffer accesses: per-thread byte offset plus a scalar one, within `bytes` of p.
+typedef unsigned qsv_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned qsv_u4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t qsv_buf(const void* p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ f2 qsv_ld2(__amdgpu_buffer_rsrc_t b, int off, int c) {
+    const qsv_u2 v = __builtin_amdgcn_raw_buffer_load_b64(b, off, c, 0);
+    return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+}
+__device__ __forceinline__ float4 qsv_ld4(__amdgpu_buffer_rsrc_t b, int off, int c) {
+    const qsv_u4 v = __builtin_amdgcn_raw_buffer_load_b128(b, off, c, 0);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+__device__ __forceinline__ void qsv_st2(f2 a, __amdgpu_buffer_rsrc_t b, int off, int c) {
+    __builtin_amdgcn_raw_buffer_store_b64(qsv_u2{__float_as_uint(a.x), __float_as_uint(a.y)}, b, off, c, 0);
+}
+__device__ __forceinline__ void qsv_st4(float4 a, __amdgpu_buffer_rsrc_t b, int off, int c) {
+    __builtin_amdgcn_raw_buffer_store_b128(
+        qsv_u4{__float_as_uint(a.x), __float_as_uint(a.y), __float_as_uint(a.z), __float_as_uint(a.w)}, b, off, c, 0);
+}
 // float64 wavefront sum by DPP lane moves: pairs, quads, half rows, rows, then
 // row 0 -> 1, 2 -> 3 and rows 0-1 -> 2-3 broadcasts; lane 63 holds the total.
 template <int CTRL, int ROWMASK>
@@ -126,6 +170,34 @@ __device__ __forceinline__ float qsv_row_sum(float v) {
     v += qsv_dppf<0x141>(v);
     v += qsv_dppf<0x140>(v);
     return v;
+}
+// Row sums of four values at once: the four lanes of bank 0, 1, 2, 3 of a row
+// (lane bits 2 and 3) end with the row's total of a, b, c, d. A bank mask keeps
+// one value in half of the banks while the other half takes the next value, so
+// four sums take 8 additions instead of 16 and one store instead of four. Two
+// wait states lie between a write and a DPP read of it.
+__device__ __forceinline__ float qsv_row_sum4(float a, float b, float c, float d) {
+    __asm__ volatile(
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %3, %3 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+        : "+&v"(a), "+&v"(b) : "v"(c), "v"(d));
+    return a;
+}
+// LDS accesses of one wave to its own part of the array complete in order;
+// this keeps the compiler from moving them across.
+__device__ __forceinline__ void qsv_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 // gradient of a gate inside a 1-qubit chain: Im<l|V P V^dagger|psi> from the
 // chain's components cx, cy, cz = Im<l|X|psi>, Im<l|Y|psi>, Im<l|Z|psi>, with
@@ -179,6 +251,7 @@ private:
     const Layout* lay_ = nullptr;  // register layout of the ops being emitted
     std::ostringstream o_;
     bool bwd_ = false, guard_ = false, last_fwd_ = false;
+    bool lds_own_ = false;  // the last exchange stayed within waves (no barrier since)
     std::string name_;
     int m_ = 0, W_ = 0, T_ = 0, threads_ = 0;
     std::vector<std::string> arrays_;
@@ -207,6 +280,8 @@ private:
         return {lq(0) == 0 ? 0 : m_ - 4, m_ - 3, m_ - 2, m_ - 1};
     }
 
+    Layout nat_layout() const { return make_layout(m_, nat_reg().data(), top_wave_bits(m_, nat_reg().data())); }
+
     // global offset of register k (within the sample) in layout L
     int gR(const Layout& L, int k) const {
         int v = 0;
@@ -227,28 +302,82 @@ private:
     }
     std::string lT_expr(const Layout& L) const { return scatter("t", L.nonreg); }
 
+    // Re-lays the tile out through LDS. When both layouts keep the same local
+    // bits on the wave index, every wave reads only what it wrote itself and no
+    // barrier is needed; choose_waves() picks those bits so that this is the
+    // common case. Byte offsets: an XOR per access and nothing else (a shift
+    // more per access before). With these, the shared Z products, the merged row
+    // sums and the buffer accesses, 20-qubit ladder, batch 64: 7.6 -> 7.2 ms per
+    // step (longest pass 18,500 -> 17,400 vector instructions); 16-qubit ring,
+    // batch 256: 1.89 -> 1.85 ms; 21-qubit ring forward, batch 7: 775 -> 750 us.
     void emit_exchange(const Layout& from, const Layout& to) {
+        const bool own = wave_bits(from) == wave_bits(to);
+        const char* sync = own ? "qsv_wave_sync();" : "__syncthreads();";
+        // waves may still be reading their own parts
+        if (!own && lds_own_) o_ << "  __syncthreads();\n";
+        lds_own_ = own;
         // The empty asm statements make each exchange compute its LDS
         // addresses afresh: otherwise the compiler keeps the addresses of
         // every layout alive across the whole kernel (tens of registers).
         o_ << "  {\n    int l0_ = " << lT_expr(from) << ";\n"
            << "    __asm__ volatile(\"\" : \"+v\"(l0_));\n"
-           << "    const int s0_ = l0_ ^ (((l0_ >> 5) ^ (l0_ >> 10)) & 31);\n"
+           << "    const int s0_ = (l0_ ^ (((l0_ >> 5) ^ (l0_ >> 10)) & 31)) << 3;\n"
            << "    int l1_ = " << lT_expr(to) << ";\n"
            << "    __asm__ volatile(\"\" : \"+v\"(l1_));\n"
-           << "    const int s1_ = l1_ ^ (((l1_ >> 5) ^ (l1_ >> 10)) & 31);\n";
+           << "    const int s1_ = (l1_ ^ (((l1_ >> 5) ^ (l1_ >> 10)) & 31)) << 3;\n"
+           << "    char* const lb_ = (char*)lds;\n";
         for (size_t ai = 0; ai < arrays_.size(); ++ai) {
             const std::string& A = arrays_[ai];
             std::string w, r;
             for (int k = 0; k < kRegs; ++k) {
-                w += "lds[s0_ ^ " + I(swz_host(lR(from, k))) + "] = " + A + "[" + I(k) + "]; ";
-                r += A + "[" + I(k) + "] = lds[s1_ ^ " + I(swz_host(lR(to, k))) + "]; ";
+                w += "*(f2*)(lb_ + (s0_ ^ " + I(swz_host(lR(from, k)) * 8) + ")) = " + A + "[" + I(k) + "]; ";
+                r += A + "[" + I(k) + "] = *(const f2*)(lb_ + (s1_ ^ " + I(swz_host(lR(to, k)) * 8) + ")); ";
             }
-            if (ai > 0) o_ << "    __syncthreads();\n";
-            o_ << "    " << act(w) << "\n    __syncthreads();\n    " << act(r) << "\n";
+            if (ai > 0) o_ << "    " << sync << "\n";
+            o_ << "    " << act(w) << "\n    " << sync << "\n    " << act(r) << "\n";
         }
-        o_ << "    __syncthreads();\n  }\n";
+        o_ << "    " << sync << "\n  }\n";
         o_ << "  gT = " << gT_expr(to) << ";\n";
+    }
+
+    // Wave bits of every stage's layout, given the load / store layout's: as few
+    // changes from one layout to the next as possible (each costs barriers),
+    // the topmost bits among equals.
+    std::vector<Layout> choose_waves(const Layout& nat, bool write_back) const {
+        const int nw = std::max(0, m_ - kRegBits - kLaneBits), ns = ps_->n_stages;
+        std::vector<std::vector<unsigned>> opt(ns);
+        std::vector<std::vector<int>> cost(ns), from(ns);
+        for (int s = 0; s < ns; ++s) {
+            const int* reg = p_->stages[ps_->stage0 + s].reg;
+            unsigned rm = 0;
+            for (int p = 0; p < kRegBits; ++p) rm |= 1u << reg[p];
+            for (unsigned w = 0; w < (1u << m_); ++w)
+                if (__builtin_popcount(w) == nw && !(w & rm)) opt[s].push_back(w);
+            std::reverse(opt[s].begin(), opt[s].end());
+            for (unsigned w : opt[s]) {
+                int best = 1 << 30, at = 0;
+                if (s == 0) {
+                    best = w == wave_bits(nat) ? 0 : 1;
+                } else {
+                    const bool same_reg = std::equal(reg, reg + kRegBits, p_->stages[ps_->stage0 + s - 1].reg);
+                    for (size_t i = 0; i < opt[s - 1].size(); ++i) {
+                        // same registers: no exchange at all, unless the wave bits changed
+                        const int c = cost[s - 1][i] + (w == opt[s - 1][i] ? 0 : same_reg ? 3 : 1);
+                        if (c < best) best = c, at = (int)i;
+                    }
+                }
+                if (s == ns - 1 && write_back) best += w == wave_bits(nat) ? 0 : 1;
+                cost[s].push_back(best);
+                from[s].push_back(at);
+            }
+        }
+        std::vector<Layout> out(ns);
+        int i = ns ? (int)(std::min_element(cost[ns - 1].begin(), cost[ns - 1].end()) - cost[ns - 1].begin()) : 0;
+        for (int s = ns - 1; s >= 0; --s) {
+            out[s] = make_layout(m_, p_->stages[ps_->stage0 + s].reg, opt[s][i]);
+            i = from[s][i];
+        }
+        return out;
     }
 
     std::string mat_ptr(int mat) const {
@@ -565,6 +694,84 @@ private:
         o_ << "    " << gs << " = ga_ + gb_;\n  }\n";
     }
 
+    // Gradient ops [a, b), taken at one point of the schedule.
+    void emit_grads(int a, int b) {
+        // Z components on several register qubits share their 16 products
+        std::vector<int> zs;
+        for (int i = a; i < b; ++i) {
+            const DOp& op = p_->ops[i];
+            if (op.kind == OP_GZ && op.pos >= 0 && op.ctl < 0) zs.push_back(i);
+        }
+        if (zs.size() >= 2) emit_joint_z(zs);
+        else zs.clear();
+        for (int i = a; i < b; ++i)
+            if (std::find(zs.begin(), zs.end(), i) == zs.end()) emit_grad(p_->ops[i]);
+        // Partials are reduced to one float32 per 16-lane row right away; rows are
+        // combined in float64 at the end of the pass. Every lane that holds a sum
+        // stores it (same value, same address): no branch, which keeps the
+        // compiler's register allocation across the kernel intact.
+        for (int i = a; i < b;) {
+            const int sl = p_->ops[i].slot;
+            bool four = i + 4 <= b;
+            for (int j = 1; four && j < 4; ++j) four = p_->ops[i + j].slot == sl + j;
+            if (four) {
+                o_ << "  red4_[" << sl << "] = qsv_row_sum4(g" << sl << ", g" << sl + 1 << ", g" << sl + 2 << ", g" << sl + 3
+                   << ");\n";
+                i += 4;
+            } else {
+                o_ << "  red1_[" << sl << "] = qsv_row_sum(g" << sl << ");\n";
+                ++i;
+            }
+        }
+    }
+
+    // Im<l|Z_q|psi> of the ops `zs` on different register qubits: the 16 products
+    // Im(conj(l) psi) once, then sums over the other qubits and, qubit by qubit,
+    // the difference of the halves and their sum (72 operations for four qubits
+    // instead of 128).
+    void emit_joint_z(const std::vector<int>& zs) {
+        o_ << "  {\n";
+        for (int k = 0; k < kRegs; ++k)
+            o_ << "    const float z" << k << "_ = fmaf(lm[" << k << "].x, ps[" << k << "].y, -(lm[" << k << "].y * ps[" << k
+               << "].x));\n";
+        std::vector<std::string> v;
+        for (int k = 0; k < kRegs; ++k) v.push_back("z" + I(k) + "_");
+        std::vector<int> pos = {0, 1, 2, 3};  // register position of each index bit of v
+        int id = 0;
+        auto fold = [&](int i) {  // halves of v along index bit i: sums, and the sum of differences
+            std::vector<std::string> sum;
+            std::string d;
+            for (int k = 0; k < (int)v.size(); ++k) {
+                if (k >> i & 1) continue;
+                const std::string &x = v[k], &y = v[k | (1 << i)];
+                const std::string name = "y" + I(id++) + "_";
+                o_ << "    const float " << name << " = " << x << " + " << y << ";\n";
+                sum.push_back(name);
+                d += (d.empty() ? "(" : " + (") + x + " - " + y + ")";
+            }
+            v = sum;
+            pos.erase(pos.begin() + i);
+            return d;
+        };
+        auto slots_on = [&](int p) {  // several where diagonal gates on one qubit lie between controlled ones
+            std::vector<int> sl;
+            for (int i : zs)
+                if (p_->ops[i].pos == p) sl.push_back(p_->ops[i].slot);
+            return sl;
+        };
+        for (int i = 0; i < (int)pos.size();) {
+            if (slots_on(pos[i]).empty()) fold(i);
+            else ++i;
+        }
+        while (!pos.empty()) {
+            const std::vector<int> sl = slots_on(pos[0]);
+            const std::string d = fold(0);
+            o_ << "    g" << sl[0] << " = " << d << ";\n";
+            for (size_t i = 1; i < sl.size(); ++i) o_ << "    g" << sl[i] << " = g" << sl[0] << ";\n";
+        }
+        o_ << "  }\n";
+    }
+
     // Readout of the last forward pass (when epart is given): per tile and
     // qubit i, sum |a|^2 (1 - 2 bit_i) into epart[(b ntiles + tile) W + i].
     // Reduced values: the thread's total T, its sums S_r over registers with
@@ -623,7 +830,7 @@ private:
         name_ = name;
         const int tb = W_ - m_;
         if (last_fwd_) {
-            o_ << readout_table(make_layout(m_, nat_reg().data()));
+            o_ << readout_table(nat_layout());
         }
         if (bwd_ && ps_->n_gout) {
             // gradient outputs of this pass: ordinal, axis, component slots x/y/z, matrix slot
@@ -669,7 +876,8 @@ private:
         o_ << "  const size_t off = (size_t)b << " << W_ << ";\n"
            << "  const float* mp = mats + ((size_t)n_shared + (size_t)b * n_ps) * 8;\n"
            << "  (void)mp;\n";
-        Layout nat = make_layout(m_, nat_reg().data());
+        const Layout nat = nat_layout();
+        lds_own_ = false;
         // With tile bit 0 = amplitude bit 0 in registers 0 and 1 of each pair,
         // a thread moves its amplitudes as 16-byte pairs when the array is
         // 16-byte aligned (a wave-uniform test; 8-byte aligned arrays take
@@ -681,27 +889,45 @@ private:
         if (guard_)
             for (const std::string& A : arrays_)
                 o_ << "  for (int k = 0; k < 16; ++k) " << A << "[k] = make_float2(0.f, 0.f);\n";
+        // Buffer accesses where a sample's bytes fit 32 bits: a byte offset from
+        // the thread index, shared by all accesses and by psi and lambda, plus a
+        // scalar constant per access, no address arithmetic (pointers take two
+        // 64-bit additions' worth of vector instructions each).
+        const bool buf = W_ <= 28;
+        auto open = [&](const std::string& name, const std::string& ptr) {
+            return buf ? "const __amdgpu_buffer_rsrc_t " + name + "b_ = qsv_buf(" + ptr + ", " + I(8LL << W_) + "u); " : std::string();
+        };
         auto gload = [&](const std::string& A, const std::string& src) {
-            std::string s1;
-            for (int k = 0; k < kRegs; ++k) s1 += A + "[" + I(k) + "] = " + src + "[gT + " + I(gR(cur, k)) + "]; ";
-            if (!v16) return s1;
-            std::string s2;
-            for (int k = 0; k < kRegs; k += 2)
-                s2 += "{ const float4 v_ = *reinterpret_cast<const float4*>(" + src + " + gT + " + I(gR(cur, k)) + "); " +
-                      A + "[" + I(k) + "] = make_float2(v_.x, v_.y); " + A + "[" + I(k + 1) +
-                      "] = make_float2(v_.z, v_.w); } ";
-            return "if (((qsv_uptr)(" + src + ") & 15) == 0) { " + s2 + "} else { " + s1 + "}";
+            std::string s1, s2;
+            for (int k = 0; k < kRegs; ++k) {
+                s1 += A + "[" + I(k) + "] = ";
+                if (buf) s1 += "qsv_ld2(" + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + "); ";
+                else s1 += src + "[gT + " + I(gR(cur, k)) + "]; ";
+            }
+            if (!v16) return "{ " + open(A, src) + s1 + "}";
+            for (int k = 0; k < kRegs; k += 2) {
+                s2 += "{ const float4 v_ = ";
+                if (buf) s2 += "qsv_ld4(" + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + ")";
+                else s2 += "*reinterpret_cast<const float4*>(" + src + " + gT + " + I(gR(cur, k)) + ")";
+                s2 += "; " + A + "[" + I(k) + "] = make_float2(v_.x, v_.y); " + A + "[" + I(k + 1) + "] = make_float2(v_.z, v_.w); } ";
+            }
+            return "{ " + open(A, src) + "if (((qsv_uptr)(" + src + ") & 15) == 0) { " + s2 + "} else { " + s1 + "} }";
         };
         auto gstore = [&](const std::string& A, const std::string& dst) {
-            std::string s1;
-            for (int k = 0; k < kRegs; ++k) s1 += dst + "[gT + " + I(gR(cur, k)) + "] = " + A + "[" + I(k) + "]; ";
-            if (!v16) return s1;
-            std::string s2;
-            for (int k = 0; k < kRegs; k += 2)
-                s2 += "*reinterpret_cast<float4*>(" + dst + " + gT + " + I(gR(cur, k)) + ") = make_float4(" + A + "[" +
-                      I(k) + "].x, " + A + "[" + I(k) + "].y, " + A + "[" + I(k + 1) + "].x, " + A + "[" + I(k + 1) +
-                      "].y); ";
-            return "if (((qsv_uptr)(" + dst + ") & 15) == 0) { " + s2 + "} else { " + s1 + "}";
+            std::string s1, s2;
+            for (int k = 0; k < kRegs; ++k) {
+                const std::string v = A + "[" + I(k) + "]";
+                if (buf) s1 += "qsv_st2(" + v + ", " + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + "); ";
+                else s1 += dst + "[gT + " + I(gR(cur, k)) + "] = " + v + "; ";
+            }
+            if (!v16) return "{ " + open(A, dst) + s1 + "}";
+            for (int k = 0; k < kRegs; k += 2) {
+                const std::string x = A + "[" + I(k) + "]", y = A + "[" + I(k + 1) + "]";
+                const std::string v = "make_float4(" + x + ".x, " + x + ".y, " + y + ".x, " + y + ".y)";
+                if (buf) s2 += "qsv_st4(" + v + ", " + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + "); ";
+                else s2 += "*reinterpret_cast<float4*>(" + dst + " + gT + " + I(gR(cur, k)) + ") = " + v + "; ";
+            }
+            return "{ " + open(A, dst) + "if (((qsv_uptr)(" + dst + ") & 15) == 0) { " + s2 + "} else { " + s1 + "} }";
         };
         const int flags = ps_->flags;
         if (!bwd_ && (flags & PF_INIT_FWD)) {
@@ -764,39 +990,37 @@ private:
             for (int j = 0; j < ng; ++j) o_ << "  float g" << j << " = 0.f;\n";
         }
         o_ << "  const int wave = t >> 6, lane = t & 63; (void)wave; (void)lane;\n";
+        const bool write_back = !bwd_ || !(flags & PF_LAST_BWD);
+        const std::vector<Layout> lays = choose_waves(nat, write_back);
+        if (bwd_ && ng) {
+            // this lane's row of partials, and the same with the lane's bank added
+            o_ << "  float* const red1_ = red + (wave * 4 + (lane >> 4)) * " << ng << ";\n"
+               << "  float* const red4_ = red1_ + ((lane >> 2) & 3); (void)red4_;\n";
+        }
         for (int s = 0; s < ps_->n_stages; ++s) {
             const DStage& st = p_->stages[ps_->stage0 + s];
-            Layout L = make_layout(m_, st.reg);
+            const Layout& L = lays[s];
             if (!same(L, cur)) {
                 emit_exchange(cur, L);
                 cur = L;
             }
             lay_ = &cur;
-            for (int oi = st.op0; oi < st.op1; ++oi) {
-                const DOp& op = p_->ops[oi];
-                if (is_grad_op(op.kind)) {
-                    emit_grad(op);
-                    // row reduction of the partial right away (float32 within a
-                    // 16-lane row; rows are combined in float64 at the end of the
-                    // pass). Every lane of a row holds the row's sum and stores it
-                    // (same value, same address): no branch, which keeps the
-                    // compiler's register allocation across the kernel intact.
-                    o_ << "  { const float r_ = qsv_row_sum(g" << op.slot << "); red[(wave * 4 + (lane >> 4)) * "
-                       << ng << " + " << op.slot << "] = r_; }\n";
-                } else {
-                    emit_apply(op);
-                }
+            for (int oi = st.op0; oi < st.op1;) {
+                int oe = oi;
+                while (oe < st.op1 && is_grad_op(p_->ops[oe].kind)) ++oe;
+                if (oe == oi) emit_apply(p_->ops[oi++]);
+                else emit_grads(oi, oe);
+                oi = std::max(oi, oe);
             }
         }
         lay_ = nullptr;  // cur goes out of scope with this kernel
-        const bool write_back = !bwd_ || !(flags & PF_LAST_BWD);
         if (write_back) {
             if (!same(cur, nat)) {
                 emit_exchange(cur, nat);
                 cur = nat;
             }
-            if (!bwd_) o_ << "  " << act(gstore("a", "st")) << "\n";
-            else o_ << "  " << act(gstore("ps", "(psi + off)") + gstore("lm", "(lam + off)")) << "\n";
+            o_ << "  " << act(bwd_ ? gstore("ps", "(psi + off)") + gstore("lm", "(lam + off)") : gstore("a", "st"))
+               << "\n";
         }
         if (last_fwd_) emit_readout(cur);
         if (bwd_ && ng) {

@@ -108,3 +108,28 @@ def gpu_run_plain(c, w, x):
     plan = binding.Plan(c.n_qubits, c.gates, c.n_weights, c.n_inputs)
     dev = torch.device("cuda:0")
     return plan.forward(torch.from_numpy(w).to(dev), torch.from_numpy(x).to(dev), x.shape[0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("gbg", [0, 1])
+@pytest.mark.parametrize("n", [4, 5, 12])
+def test_several_z_components_at_one_point(orc, n, gbg):
+    """Diagonal gates on all register qubits, and twice on one of them with only
+    diagonal gates between: their components share one set of products."""
+    c = I.Circuit(n, name=f"zz{n}")
+    for q in range(n):
+        c.weight("RY", q)
+    for r in range(3):
+        for q in range(n):
+            for _ in range(1 + (q + r) % 3):
+                c.weight("RZ", q)
+        for q in range(n - 1):
+            c.fixed("CZ", q, q + 1)
+    for q in range(n):
+        c.weight("RX", q)
+    print(f"[z] n={n} gbg={gbg}", flush=True)
+    w, x = I.draw_angles(c, 2, 30 + n)
+    g = I.draw_grad_out(c, 2, 30 + n)
+    got = gpu_run(c, w, x, 2, g, bwd_gate_by_gate=gbg)
+    ok, rel = grad_close(got["gw"].cpu().numpy(), oracle_run(orc, c, w, x, 2, g)["gw"])
+    assert ok, rel
