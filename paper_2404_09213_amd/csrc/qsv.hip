@@ -30,6 +30,7 @@
 #include <map>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <unordered_set>
 
 #include "jit.hpp"
@@ -172,9 +173,10 @@ __device__ __forceinline__ double re_conj_mul(double2 l, double2 p) { return l.x
 // Bank-conflict swizzle of a tile-local amplitude index (bijection on [0, 2^m)).
 __device__ __forceinline__ int swz(int l) { return l ^ (((l >> 5) ^ (l >> 10)) & 31); }
 
-__device__ __forceinline__ int64_t insert_bit(int64_t x, int s, int v) {
-    const int64_t lo = x & ((int64_t(1) << s) - 1);
-    return ((x >> s) << (s + 1)) | (int64_t(v) << s) | lo;
+template <class I>
+__device__ __forceinline__ I insert_bit(I x, int s, int v) {
+    const I lo = x & ((I(1) << s) - 1);
+    return ((x >> s) << (s + 1)) | (I(v) << s) | lo;
 }
 
 // Launch shape of a one-dimensional grid of n_blocks blocks. HIP bounds the
@@ -532,7 +534,8 @@ __global__ __launch_bounds__(256) void k_expval_final(const double* __restrict__
 // ----------------------------------------------------------------------------
 // gradient reduction: partials[(ordinal * B + b) * nch + chunk]
 // ----------------------------------------------------------------------------
-// Partial of ordinal o, sample b, chunk k at part[B * pu[o] + b * nch[o] + k].
+// Partial of ordinal o, sample b, chunk k at part[B * pu[o] + b * nch[o] + k];
+// with nch1 > 0 every ordinal has nch1 chunks instead.
 __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ part,
                                                      const int32_t* __restrict__ csr, int n_weights,
                                                      int n_inputs, int B,
@@ -540,7 +543,7 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ 
                                                      const int32_t* __restrict__ nchv,
                                                      double* __restrict__ gw,
                                                      double* __restrict__ gx,
-                                                     const float* __restrict__ weights, int remap) {
+                                                     const float* __restrict__ weights, int remap, int64_t nch1) {
     __shared__ double red[256];
     const int t = threadIdx.x;
     const int o = blockIdx.x;  // output index: weights first, then (b, input)
@@ -566,9 +569,9 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ 
     }
     for (int l = 0; l < nl; ++l) {
         const int o = list[l];
-        const int64_t nch = nchv[o];
+        const int64_t nch = nch1 > 0 ? nch1 : nchv[o];
         const int64_t per = (int64_t)(b1 - b0) * nch;
-        const double* base = part + (int64_t)B * pu[o] + (int64_t)b0 * nch;
+        const double* base = part + (int64_t)B * (nch1 > 0 ? o * nch1 : pu[o]) + (int64_t)b0 * nch;
         for (int64_t e = t; e < per; e += 256) s += base[e];
     }
     red[t] = s;
@@ -628,7 +631,7 @@ struct PgBits {
     int sh[3], val[3];  // ascending shifts
 };
 
-__device__ __forceinline__ PgBits pg_bits(const PGate& pg) {
+__host__ __device__ __forceinline__ PgBits pg_bits(const PGate& pg) {
     PgBits r;
     r.n = 0;
     auto add = [&](int sh, int v) {
@@ -651,8 +654,11 @@ __device__ __forceinline__ PgBits pg_bits(const PGate& pg) {
 }
 
 // index of item `it` among the indices whose fixed bits take their values
-__device__ __forceinline__ int64_t pg_index(int64_t it, const PgBits& f) {
-    for (int i = 0; i < f.n; ++i) it = insert_bit(it, f.sh[i], f.val[i]);
+template <class I>
+__device__ __forceinline__ I pg_index(I it, const PgBits& f) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (i < f.n) it = insert_bit(it, f.sh[i], f.val[i]);
     return it;
 }
 
@@ -663,7 +669,7 @@ __device__ __forceinline__ bool pg_ctl_ok(const PGate& pg, int64_t idx) {
 
 template <class V>
 __global__ __launch_bounds__(256) void k_pg_apply(V* __restrict__ state, int W, int64_t B,
-                                                  PGate pg, const Real<V>* __restrict__ mats,
+                                                  PGate pg, PgBits f, const Real<V>* __restrict__ mats,
                                                   int n_shared, int n_ps) {
     // kPgItems items per thread, 256 apart (coalesced). Items touch disjoint
     // amplitudes, so every load of the thread is issued before the first store:
@@ -687,7 +693,6 @@ __global__ __launch_bounds__(256) void k_pg_apply(V* __restrict__ state, int W, 
             state[it] = cmul(ph, a[i]);
         }
     } else if (pg.cls == OP_SIGN) {
-        const PgBits f = pg_bits(pg);
         const int64_t total = B << (W - f.n);
         V a[kPgItems];
         int64_t idx[kPgItems];
@@ -701,7 +706,6 @@ __global__ __launch_bounds__(256) void k_pg_apply(V* __restrict__ state, int W, 
         for (int i = 0; i < kPgItems; ++i)
             if (idx[i] >= 0) state[idx[i]] = mkc(-a[i].x, -a[i].y);
     } else {
-        const PgBits f = pg_bits(pg);
         const int64_t total = B << (W - f.n);
         const int64_t step = int64_t(1) << pg.tsh;
         V x[kPgItems], y[kPgItems];
@@ -727,6 +731,39 @@ __global__ __launch_bounds__(256) void k_pg_apply(V* __restrict__ state, int W, 
     }
 }
 
+// One item per thread and one sample per grid row: an amplitude (diagonal and
+// sign gates, over the amplitudes their controls select) or a pair. Samples with
+// at least 256 items, complex128 (an amplitude is 16 bytes by itself) or what
+// 16-byte accesses cannot do: with the sample uniform over a block the matrix
+// comes by scalar loads. The flat kernel above loads it per thread and gives a thread four
+// items, which leaves the chip part empty up to 2^20 amplitudes or so (15
+// qubits, batch 8, bound by latency: 11.4 -> 3.1 us per gate).
+template <class V>
+__global__ __launch_bounds__(256) void k_pg_apply_one(V* __restrict__ state, int W, PGate pg, PgBits f,
+                                                      const Real<V>* __restrict__ mats, int n_shared, int n_ps) {
+    const int b = blockIdx.y;
+    unsigned i = blockIdx.x * 256u + threadIdx.x;
+    if (i >> (W - f.n)) return;
+    i = pg_index(i, f);
+    V* st = state + ((size_t)b << W) + i;
+    if (pg.cls == OP_SIGN) {
+        const V a = *st;
+        *st = mkc(-a.x, -a.y);
+        return;
+    }
+    M2T<V> M{};
+    if (pg.cls != OP_SWAP) M = load_m2(mat_ptr(mats, pg.mat, b, n_shared, n_ps));
+    if (pg.cls == OP_DIAG) {
+        *st = cmul(((i >> pg.tsh) & 1u) ? M.m11 : M.m00, *st);
+        return;
+    }
+    V* st1 = st + ((size_t)1 << pg.tsh);
+    V x = *st, y = *st1;
+    pair_apply(pg.cls, M, x, y);
+    *st = x;
+    *st1 = y;
+}
+
 // 16-byte access modes of a complex64 per-gate launch (chosen on the host):
 //  PG_VEC_PAIRS  every index bit the gate fixes is above bit 0, so item i covers
 //                the gate's items 2i and 2i+1, whose amplitudes sit next to each
@@ -742,13 +779,22 @@ __global__ __launch_bounds__(256) void k_pg_apply(V* __restrict__ state, int W, 
 //                fixed bits are all 1 negated, and everything written back with
 //                full 16-byte stores.
 enum { PG_SCALAR = 0, PG_VEC_PAIRS = 1, PG_VEC_ADJ = 2, PG_VEC_SWEEP = 3 };
-__device__ __forceinline__ f4v ntl4(const float2* p) { return __builtin_nontemporal_load((const f4v*)p); }
+// NT: non-temporal, for states that no cache holds until the next gate (see pg_stream)
+template <bool NT>
+__device__ __forceinline__ f4v ldv(const float2* p) {
+    return NT ? __builtin_nontemporal_load((const f4v*)p) : *(const f4v*)p;
+}
 // cached load: for a pair whose two halves share a cache line (target bit <= 3),
 // where a streaming load of the second half would fetch the line again
+template <bool NT>
 __device__ __forceinline__ f4v ld4(const float2* p, bool cached) {
-    return cached ? *(const f4v*)p : __builtin_nontemporal_load((const f4v*)p);
+    return NT && !cached ? __builtin_nontemporal_load((const f4v*)p) : *(const f4v*)p;
 }
-__device__ __forceinline__ void nts4(float2* p, f4v v) { __builtin_nontemporal_store(v, (f4v*)p); }
+template <bool NT>
+__device__ __forceinline__ void stv(float2* p, f4v v) {
+    if (NT) __builtin_nontemporal_store(v, (f4v*)p);
+    else *(f4v*)p = v;
+}
 __device__ __forceinline__ float2 lo2(f4v v) { return make_float2(v.x, v.y); }
 __device__ __forceinline__ float2 hi2(f4v v) { return make_float2(v.z, v.w); }
 __device__ __forceinline__ f4v cat2(float2 a, float2 b) { return f4v{a.x, a.y, b.x, b.y}; }
@@ -761,56 +807,71 @@ __device__ __forceinline__ bool sign_on(const PgBits& f, int64_t idx) {
 
 // One item per thread, 16-byte accesses (see PG_VEC_*). Items: diagonal B 2^W / 2,
 // sign and pair updates B 2^(W - fixed) / 2 (PAIRS) or B 2^(W - fixed) (ADJ).
+//
+// ROWS: one grid row per sample, whose items (a power of two, at least 256)
+// fill its blocks: the matrix comes by scalar loads, indices are 32 bits,
+// and the fixed bits come from the host: sorted by every thread, they cost more
+// than the sweep (18 qubits, batch 16, 32 MiB: 20.6 -> 8.5 us per gate over the
+// whole ladder). Smaller samples share blocks in one flat grid.
+template <bool ROWS, bool NT>
 __global__ __launch_bounds__(256) void k_pg_apply_vec(float2* __restrict__ state, int W, int64_t items,
-                                                      PGate pg, int mode, const float* __restrict__ mats,
+                                                      PGate pg, PgBits f, int mode, const float* __restrict__ mats,
                                                       int n_shared, int n_ps, int rev) {
-    const int64_t blk = rev ? (int64_t)gridDim.x * gridDim.y - 1 - block_1d() : block_1d();
-    const int64_t it = blk * 256 + threadIdx.x;
-    if (it >= items) return;
+    using Ix = std::conditional_t<ROWS, unsigned, int64_t>;
+    int row = 0;
+    Ix it;
+    if (ROWS) {
+        row = rev ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y;
+        it = (rev ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * 256u + threadIdx.x;
+        state += (size_t)row << W;
+    } else {
+        const int64_t blk = rev ? (int64_t)gridDim.x * gridDim.y - 1 - block_1d() : block_1d();
+        it = (Ix)(blk * 256 + threadIdx.x);
+        if ((int64_t)it >= items) return;
+    }
+    auto matrix = [&](Ix i) { return load_m2(mat_ptr(mats, pg.mat, ROWS ? row : (int)((int64_t)i >> W), n_shared, n_ps)); };
     if (pg.cls == OP_DIAG) {
-        const int64_t i0 = 2 * it;
-        const int b = (int)(i0 >> W);
-        const M2 M = load_m2(mat_ptr(mats, pg.mat, b, n_shared, n_ps));
-        const f4v a = ntl4(state + i0);
+        const Ix i0 = 2 * it;
+        const M2 M = matrix(i0);
+        const f4v a = ldv<NT>(state + i0);
         float2 u = lo2(a), v = hi2(a);
         if (pg_ctl_ok(pg, i0)) u = cmul(((i0 >> pg.tsh) & 1) ? M.m11 : M.m00, u);
         if (pg_ctl_ok(pg, i0 + 1)) v = cmul((((i0 + 1) >> pg.tsh) & 1) ? M.m11 : M.m00, v);
-        nts4(state + i0, cat2(u, v));
+        stv<NT>(state + i0, cat2(u, v));
         return;
     }
-    const PgBits f = pg_bits(pg);
     if (pg.cls == OP_SIGN) {
         if (mode == PG_VEC_SWEEP) {
-            const int64_t i0 = 2 * it;
+            const Ix i0 = 2 * it;
             const bool n0 = sign_on(f, i0), n1 = sign_on(f, i0 + 1);
-            const f4v a = ntl4(state + i0);
-            nts4(state + i0, f4v{n0 ? -a.x : a.x, n0 ? -a.y : a.y, n1 ? -a.z : a.z, n1 ? -a.w : a.w});
+            const f4v a = ldv<NT>(state + i0);
+            stv<NT>(state + i0, f4v{n0 ? -a.x : a.x, n0 ? -a.y : a.y, n1 ? -a.z : a.z, n1 ? -a.w : a.w});
             return;
         }
-        const int64_t i0 = pg_index(2 * it, f);  // with its neighbour i0 + 1
-        const f4v a = ntl4(state + i0);
-        nts4(state + i0, f4v{-a.x, -a.y, -a.z, -a.w});
+        const Ix i0 = pg_index(Ix(2 * it), f);  // with its neighbour i0 + 1
+        const f4v a = ldv<NT>(state + i0);
+        stv<NT>(state + i0, f4v{-a.x, -a.y, -a.z, -a.w});
         return;
     }
     M2 M{};
     if (mode == PG_VEC_ADJ) {
-        const int64_t i0 = pg_index(it, f);
-        if (pg.cls != OP_SWAP) M = load_m2(mat_ptr(mats, pg.mat, (int)(i0 >> W), n_shared, n_ps));
-        const f4v a = ntl4(state + i0);
+        const Ix i0 = pg_index(it, f);
+        if (pg.cls != OP_SWAP) M = matrix(i0);
+        const f4v a = ldv<NT>(state + i0);
         float2 x = lo2(a), y = hi2(a);
         pair_apply(pg.cls, M, x, y);
-        nts4(state + i0, cat2(x, y));
+        stv<NT>(state + i0, cat2(x, y));
         return;
     }
-    const int64_t i0 = pg_index(2 * it, f), i1 = i0 | (int64_t(1) << pg.tsh);
-    if (pg.cls != OP_SWAP) M = load_m2(mat_ptr(mats, pg.mat, (int)(i0 >> W), n_shared, n_ps));
+    const Ix i0 = pg_index(Ix(2 * it), f), i1 = i0 | (Ix(1) << pg.tsh);
+    if (pg.cls != OP_SWAP) M = matrix(i0);
     const bool near = pg.tsh <= 3;
-    const f4v a = ld4(state + i0, near), c = ld4(state + i1, near);
+    const f4v a = ld4<NT>(state + i0, near), c = ld4<NT>(state + i1, near);
     float2 x0 = lo2(a), x1 = hi2(a), y0 = lo2(c), y1 = hi2(c);
     pair_apply(pg.cls, M, x0, y0);
     pair_apply(pg.cls, M, x1, y1);
-    nts4(state + i0, cat2(x0, x1));
-    nts4(state + i1, cat2(y0, y1));
+    stv<NT>(state + i0, cat2(x0, x1));
+    stv<NT>(state + i1, cat2(y0, y1));
 }
 
 // lambda = D psi_N with D(idx) = sum_i g[b,i] (1 - 2 bit_i(idx)) = G - 2 sum over
@@ -864,7 +925,7 @@ __global__ __launch_bounds__(256) void k_adj_init(const V* __restrict__ psiN,
 // then psi <- U^dagger psi, lambda <- U^dagger lambda. Grid (nch, B).
 template <class V>
 __global__ __launch_bounds__(256) void k_pg_adj(V* __restrict__ psi, V* __restrict__ lam,
-                                                int W, int B, PGate pg,
+                                                int W, int B, PGate pg, PgBits f,
                                                 const Real<V>* __restrict__ mats, int n_shared,
                                                 int n_ps, double* __restrict__ part, int64_t nch) {
     __shared__ double red[4];
@@ -877,11 +938,11 @@ __global__ __launch_bounds__(256) void k_pg_adj(V* __restrict__ psi, V* __restri
     Real<V> acc = 0;
     M2T<V> M{};
     if (pg.cls != OP_SWAP && pg.cls != OP_SIGN) M = load_m2(mat_ptr(mats, pg.mat, b, n_shared, n_ps));
+    // items of the chunk: amplitudes that a diagonal or sign gate touches, or pairs
+    const unsigned per = (unsigned)((int64_t(1) << (W - f.n)) / nch), first = (unsigned)chunk * per;
     if (pg.cls == OP_DIAG) {
-        const int64_t n = int64_t(1) << W, per = n / nch;
-        for (int64_t e = t; e < per; e += 256) {
-            const int64_t idx = chunk * per + e;
-            if (!pg_ctl_ok(pg, idx)) continue;
+        for (unsigned e = t; e < per; e += 256) {
+            const unsigned idx = pg_index(first + e, f);
             const int bit = (idx >> pg.tsh) & 1;
             V p = P[idx], l = L[idx];
             if (pg.grad == OP_GZ) acc += bit ? -im_conj_mul(l, p) : im_conj_mul(l, p);
@@ -890,21 +951,16 @@ __global__ __launch_bounds__(256) void k_pg_adj(V* __restrict__ psi, V* __restri
             L[idx] = cmul(ph, l);
         }
     } else if (pg.cls == OP_SIGN) {
-        const PgBits f = pg_bits(pg);
-        const int64_t n = int64_t(1) << (W - f.n), per = n / nch;
-        for (int64_t e = t; e < per; e += 256) {
-            const int64_t idx = pg_index(chunk * per + e, f);
+        for (unsigned e = t; e < per; e += 256) {
+            const unsigned idx = pg_index(first + e, f);
             const V p = P[idx], l = L[idx];
             P[idx] = mkc(-p.x, -p.y);
             L[idx] = mkc(-l.x, -l.y);
         }
     } else {
-        const PgBits f = pg_bits(pg);
-        const int64_t n = int64_t(1) << (W - f.n), per = n / nch;
-        for (int64_t e = t; e < per; e += 256) {
-            const int64_t it = chunk * per + e;
-            const int64_t i0 = pg_index(it, f);
-            const int64_t i1 = i0 | (int64_t(1) << pg.tsh);
+        for (unsigned e = t; e < per; e += 256) {
+            const unsigned i0 = pg_index(first + e, f);
+            const unsigned i1 = i0 | (1u << pg.tsh);
             V p0 = P[i0], p1 = P[i1], l0 = L[i0], l1 = L[i1];
             if (pg.grad == OP_GX) acc += im_conj_mul(l0, p1) + im_conj_mul(l1, p0);
             else if (pg.grad == OP_GY) acc += re_conj_mul(l1, p0) - re_conj_mul(l0, p1);
@@ -923,15 +979,16 @@ __global__ __launch_bounds__(256) void k_pg_adj(V* __restrict__ psi, V* __restri
 
 // Plain-method backward step with 16-byte accesses (complex64, PG_VEC_* modes
 // as in k_pg_apply_vec): same arithmetic, partials and grid as k_pg_adj.
+template <bool NT>
 __global__ __launch_bounds__(256) void k_pg_adj_vec(float2* __restrict__ psi, float2* __restrict__ lam, int W,
-                                                    int B, PGate pg, int mode, const float* __restrict__ mats,
+                                                    int B, PGate pg, PgBits f, int mode, const float* __restrict__ mats,
                                                     int n_shared, int n_ps, double* __restrict__ part,
                                                     int64_t nch, int rev) {
     __shared__ double red[4];
     constexpr int nt = 256;
     const int t = threadIdx.x;
     const int b = rev ? (int)gridDim.y - 1 - (int)blockIdx.y : (int)blockIdx.y;
-    const int64_t chunk = rev ? (int64_t)gridDim.x - 1 - blockIdx.x : (int64_t)blockIdx.x;
+    const unsigned chunk = rev ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
     const size_t off = (size_t)b << W;
     float2* P = psi + off;
     float2* L = lam + off;
@@ -943,14 +1000,14 @@ __global__ __launch_bounds__(256) void k_pg_adj_vec(float2* __restrict__ psi, fl
         else if (pg.grad == OP_GY) acc += re_conj_mul(l1, p0) - re_conj_mul(l0, p1);
     };
     if (pg.cls == OP_DIAG) {
-        const int64_t per = ((int64_t(1) << W) / 2) / nch;  // items of two amplitudes
-        for (int64_t e = t; e < per; e += nt) {
-            const int64_t i0 = 2 * (chunk * per + e);
-            const f4v pa = ntl4(P + i0), la = ntl4(L + i0);
+        const unsigned per = (unsigned)(((int64_t(1) << W) / 2) / nch);  // items of two amplitudes
+        for (unsigned e = t; e < per; e += nt) {
+            const unsigned i0 = 2 * (chunk * per + e);
+            const f4v pa = ldv<NT>(P + i0), la = ldv<NT>(L + i0);
             float2 p[2] = {lo2(pa), hi2(pa)}, l[2] = {lo2(la), hi2(la)};
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int64_t idx = i0 + j;
+                const unsigned idx = i0 + j;
                 if (!pg_ctl_ok(pg, idx)) continue;
                 const int bit = (idx >> pg.tsh) & 1;
                 if (pg.grad == OP_GZ) acc += bit ? -im_conj_mul(l[j], p[j]) : im_conj_mul(l[j], p[j]);
@@ -958,49 +1015,45 @@ __global__ __launch_bounds__(256) void k_pg_adj_vec(float2* __restrict__ psi, fl
                 p[j] = cmul(ph, p[j]);
                 l[j] = cmul(ph, l[j]);
             }
-            nts4(P + i0, cat2(p[0], p[1]));
-            nts4(L + i0, cat2(l[0], l[1]));
+            stv<NT>(P + i0, cat2(p[0], p[1]));
+            stv<NT>(L + i0, cat2(l[0], l[1]));
         }
     } else if (pg.cls == OP_SIGN && mode == PG_VEC_SWEEP) {
-        const PgBits f = pg_bits(pg);
-        const int64_t per = ((int64_t(1) << W) / 2) / nch;
-        for (int64_t e = t; e < per; e += nt) {
-            const int64_t i0 = 2 * (chunk * per + e);
+        const unsigned per = (unsigned)(((int64_t(1) << W) / 2) / nch);
+        for (unsigned e = t; e < per; e += nt) {
+            const unsigned i0 = 2 * (chunk * per + e);
             const bool n0 = sign_on(f, i0), n1 = sign_on(f, i0 + 1);
-            const f4v pa = ntl4(P + i0), la = ntl4(L + i0);
-            nts4(P + i0, f4v{n0 ? -pa.x : pa.x, n0 ? -pa.y : pa.y, n1 ? -pa.z : pa.z, n1 ? -pa.w : pa.w});
-            nts4(L + i0, f4v{n0 ? -la.x : la.x, n0 ? -la.y : la.y, n1 ? -la.z : la.z, n1 ? -la.w : la.w});
+            const f4v pa = ldv<NT>(P + i0), la = ldv<NT>(L + i0);
+            stv<NT>(P + i0, f4v{n0 ? -pa.x : pa.x, n0 ? -pa.y : pa.y, n1 ? -pa.z : pa.z, n1 ? -pa.w : pa.w});
+            stv<NT>(L + i0, f4v{n0 ? -la.x : la.x, n0 ? -la.y : la.y, n1 ? -la.z : la.z, n1 ? -la.w : la.w});
         }
     } else if (pg.cls == OP_SIGN) {
-        const PgBits f = pg_bits(pg);
-        const int64_t per = ((int64_t(1) << (W - f.n)) / 2) / nch;
-        for (int64_t e = t; e < per; e += nt) {
-            const int64_t i0 = pg_index(2 * (chunk * per + e), f);
-            const f4v pa = ntl4(P + i0), la = ntl4(L + i0);
-            nts4(P + i0, f4v{-pa.x, -pa.y, -pa.z, -pa.w});
-            nts4(L + i0, f4v{-la.x, -la.y, -la.z, -la.w});
+        const unsigned per = (unsigned)(((int64_t(1) << (W - f.n)) / 2) / nch);
+        for (unsigned e = t; e < per; e += nt) {
+            const unsigned i0 = pg_index(2 * (chunk * per + e), f);
+            const f4v pa = ldv<NT>(P + i0), la = ldv<NT>(L + i0);
+            stv<NT>(P + i0, f4v{-pa.x, -pa.y, -pa.z, -pa.w});
+            stv<NT>(L + i0, f4v{-la.x, -la.y, -la.z, -la.w});
         }
     } else if (mode == PG_VEC_ADJ) {
-        const PgBits f = pg_bits(pg);
-        const int64_t per = (int64_t(1) << (W - f.n)) / nch;
-        for (int64_t e = t; e < per; e += nt) {
-            const int64_t i0 = pg_index(chunk * per + e, f);
-            const f4v pa = ntl4(P + i0), la = ntl4(L + i0);
+        const unsigned per = (unsigned)((int64_t(1) << (W - f.n)) / nch);
+        for (unsigned e = t; e < per; e += nt) {
+            const unsigned i0 = pg_index(chunk * per + e, f);
+            const f4v pa = ldv<NT>(P + i0), la = ldv<NT>(L + i0);
             float2 p0 = lo2(pa), p1 = hi2(pa), l0 = lo2(la), l1 = hi2(la);
             grad_pair(p0, p1, l0, l1);
             pair_apply(pg.cls, M, p0, p1);
             pair_apply(pg.cls, M, l0, l1);
-            nts4(P + i0, cat2(p0, p1));
-            nts4(L + i0, cat2(l0, l1));
+            stv<NT>(P + i0, cat2(p0, p1));
+            stv<NT>(L + i0, cat2(l0, l1));
         }
     } else {
-        const PgBits f = pg_bits(pg);
-        const int64_t per = ((int64_t(1) << (W - f.n)) / 2) / nch;
-        const int64_t step = int64_t(1) << pg.tsh;
+        const unsigned per = (unsigned)(((int64_t(1) << (W - f.n)) / 2) / nch);
+        const unsigned step = 1u << pg.tsh;
         const bool near = pg.tsh <= 3;
-        for (int64_t e = t; e < per; e += nt) {
-            const int64_t i0 = pg_index(2 * (chunk * per + e), f), i1 = i0 | step;
-            const f4v pa = ld4(P + i0, near), pc = ld4(P + i1, near), la = ld4(L + i0, near), lc = ld4(L + i1, near);
+        for (unsigned e = t; e < per; e += nt) {
+            const unsigned i0 = pg_index(2 * (chunk * per + e), f), i1 = i0 | step;
+            const f4v pa = ld4<NT>(P + i0, near), pc = ld4<NT>(P + i1, near), la = ld4<NT>(L + i0, near), lc = ld4<NT>(L + i1, near);
             float2 p00 = lo2(pa), p01 = hi2(pa), p10 = lo2(pc), p11 = hi2(pc);
             float2 l00 = lo2(la), l01 = hi2(la), l10 = lo2(lc), l11 = hi2(lc);
             grad_pair(p00, p10, l00, l10);
@@ -1009,10 +1062,10 @@ __global__ __launch_bounds__(256) void k_pg_adj_vec(float2* __restrict__ psi, fl
             pair_apply(pg.cls, M, p01, p11);
             pair_apply(pg.cls, M, l00, l10);
             pair_apply(pg.cls, M, l01, l11);
-            nts4(P + i0, cat2(p00, p01));
-            nts4(P + i1, cat2(p10, p11));
-            nts4(L + i0, cat2(l00, l01));
-            nts4(L + i1, cat2(l10, l11));
+            stv<NT>(P + i0, cat2(p00, p01));
+            stv<NT>(P + i1, cat2(p10, p11));
+            stv<NT>(L + i0, cat2(l00, l01));
+            stv<NT>(L + i1, cat2(l10, l11));
         }
     }
     if (pg.slot >= 0) {
@@ -2076,9 +2129,15 @@ size_t fwd_mats_bytes(const qsv_plan_t* p, int64_t B) {
     return align256(((size_t)p->ref_shared + (size_t)B * p->ref_ps) * 8 * (amp_size(p) / 2) + 32);
 }
 
-int64_t grad_nch(const qsv_plan_t* p) {
-    return p->opts.method == QSV_METHOD_PER_GATE ? pg_chunks(p->W)
-                                                 : int64_t(1) << (p->W - std::min(p->opts.tile_qubits, p->W));
+// Chunks per sample of the plain method's backward launches and partials: as
+// planned (4096 amplitudes each) where these fill the chip, else up to eight
+// times as many, so that a thread has at least one pair (15 qubits, batch 8,
+// complex128, 64 -> 512 blocks: 8.0 -> 4.4 us per gate; 18 qubits, batch 16
+// has 1,024 blocks, and 2,048 or 4,096 made no difference).
+int64_t pg_nch(const qsv_plan_t* p, int64_t B) {
+    int64_t nch = pg_chunks(p->W);
+    while (nch * B < 512 && nch < (int64_t(1) << std::max(p->W - 9, 0))) nch *= 2;
+    return nch;
 }
 
 int64_t expval_nchunk(const qsv_plan_t* p) { return int64_t(1) << (p->W - std::min(p->W, 12)); }
@@ -2095,7 +2154,8 @@ size_t state_bytes(const qsv_plan_t* p, int64_t B) { return (size_t)B * (size_t)
 constexpr size_t kLamSkew = 4096 + 256;
 
 size_t partial_bytes(const qsv_plan_t* p, int64_t B) {
-    return align256((size_t)std::max<int64_t>(p->pu_total, 1) * B * sizeof(double));
+    const int64_t per = p->opts.method == QSV_METHOD_PER_GATE && !p->multi ? p->n_param * pg_nch(p, B) : p->pu_total;
+    return align256((size_t)std::max<int64_t>(per, 1) * B * sizeof(double));
 }
 
 
@@ -2333,6 +2393,21 @@ int pg_reverse(const PGate& pg, int vmode, size_t i, int64_t state_bytes) {
 int pg_fixed_bits(const PGate& g) {
     const int nctl = (g.csh >= 0) + (g.csh2 >= 0);
     return g.cls == OP_SIGN ? 2 + (g.csh2 >= 0) : 1 + nctl;
+}
+
+// Whether the states (psi alone, or psi and lambda) are too large for the 256 MB
+// Infinity Cache to hold a part of them that is worth keeping until the next
+// gate: then accesses are non-temporal (20 qubits, batch 64, 512 MiB: 6.8
+// against 6.2 TB/s for a streaming probe), else cached (18 qubits, batch 16,
+// psi and lambda 64 MiB: adjoint 22.0 -> 20.7 us per gate).
+bool pg_stream(int64_t bytes) { return bytes > (int64_t(256) << 20); }
+
+// Index bits fixed by an item of k_pg_apply_one: a diagonal gate's items are
+// the amplitudes its controls select.
+PgBits pg_one_bits(const PGate& g) {
+    PGate x = g;
+    if (g.cls == OP_DIAG) x.tsh = -1;
+    return pg_bits(x);
 }
 
 double pg_touched(const PGate& g) {
@@ -2668,14 +2743,28 @@ static int forward_impl(const qsv_plan_t* p, const float* w, const float* x, int
                 // one item per thread: two amplitudes (diagonal), two pairs (PAIRS) or one pair (ADJ)
                 const int64_t vitems = (pg.cls == OP_DIAG || vmode == PG_VEC_SWEEP) ? (B << W) / 2
                                      : vmode == PG_VEC_ADJ ? (B << (W - nfix)) : (B << (W - nfix)) / 2;
-                hipLaunchKernelGGL(k_pg_apply_vec, grid_1d((vitems + 255) / 256), dim3(256), 0, s, st, W,
-                                   vitems, pg, vmode, (const float*)mats, p->n_shared_mats[0], p->n_ps_mats[0],
+                const int64_t sitems = vitems / B;
+                const bool rows = sitems >= 256, nt = pg_stream((int64_t)state_bytes(p, B));
+                const dim3 grid = rows ? dim3((unsigned)(sitems / 256), (unsigned)B) : grid_1d((vitems + 255) / 256);
+                auto* k = rows ? (nt ? k_pg_apply_vec<true, true> : k_pg_apply_vec<true, false>)
+                               : (nt ? k_pg_apply_vec<false, true> : k_pg_apply_vec<false, false>);
+                hipLaunchKernelGGL(k, grid, dim3(256), 0, s, st, W, vitems, pg, pg_bits(pg), vmode, (const float*)mats,
+                                   p->n_shared_mats[0], p->n_ps_mats[0],
                                    pg_reverse(pg, vmode, i, (int64_t)state_bytes(p, B)));
+            } else if (W - pg_one_bits(pg).n >= 8) {
+                const PgBits f = pg_one_bits(pg);
+                const dim3 grid(1u << (W - f.n - 8), (unsigned)B);
+                if (c128(p))
+                    hipLaunchKernelGGL(k_pg_apply_one<double2>, grid, dim3(256), 0, s, (double2*)st, W, pg, f,
+                                       (const double*)mats, p->n_shared_mats[0], p->n_ps_mats[0]);
+                else
+                    hipLaunchKernelGGL(k_pg_apply_one<float2>, grid, dim3(256), 0, s, st, W, pg, f, (const float*)mats,
+                                       p->n_shared_mats[0], p->n_ps_mats[0]);
             } else if (c128(p)) {
                 hipLaunchKernelGGL(k_pg_apply<double2>, grid_1d(blocks), dim3(256), 0, s, (double2*)st, W,
-                                   B, pg, (const double*)mats, p->n_shared_mats[0], p->n_ps_mats[0]);
+                                   B, pg, pg_bits(pg), (const double*)mats, p->n_shared_mats[0], p->n_ps_mats[0]);
             } else {
-                hipLaunchKernelGGL(k_pg_apply<float2>, grid_1d(blocks), dim3(256), 0, s, st, W, B, pg,
+                hipLaunchKernelGGL(k_pg_apply<float2>, grid_1d(blocks), dim3(256), 0, s, st, W, B, pg, pg_bits(pg),
                                    (const float*)mats, p->n_shared_mats[0], p->n_ps_mats[0]);
             }
             prof_end(p, s, ev, K_PG_APPLY, 2.0 * (double)amp_size(p) * touched * amps, p->pg_fwd_flops[i] * amps,
@@ -2904,7 +2993,7 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
     double* part = (double*)c;
     c += partial_bytes(p, B);
     if ((rc = run_coef(p, T, 1, w, x, B, mats, s))) return rc;
-    const int64_t nch = grad_nch(p);
+    const int64_t nch = pg_nch(p, B);  // plain method
     const double amps = (double)B * (double)(int64_t(1) << W);
     if (p->multi) {
         DeviceTables::Queue* Q;
@@ -2945,16 +3034,17 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
             ev = prof_begin(p, s);
             const int vmode = pg_vec_mode(p, pg, psi);
             if (vmode != PG_SCALAR)
-                hipLaunchKernelGGL(k_pg_adj_vec, dim3((unsigned)nch, (unsigned)B), dim3(256), 0, s, psi, lam, W,
-                                   (int)B, pg, vmode, (const float*)mats, p->n_shared_mats[1], p->n_ps_mats[1], part,
+                hipLaunchKernelGGL(pg_stream(2 * (int64_t)state_bytes(p, B)) ? k_pg_adj_vec<true> : k_pg_adj_vec<false>,
+                                   dim3((unsigned)nch, (unsigned)B), dim3(256), 0, s, psi, lam, W,
+                                   (int)B, pg, pg_bits(pg), vmode, (const float*)mats, p->n_shared_mats[1], p->n_ps_mats[1], part,
                                    nch, pg_reverse(pg, vmode, i, (int64_t)state_bytes(p, B)));
             else if (c128(p))
                 hipLaunchKernelGGL(k_pg_adj<double2>, dim3((unsigned)nch, (unsigned)B), dim3(256), 0, s,
-                                   (double2*)psi, (double2*)lam, W, (int)B, pg, (const double*)mats,
+                                   (double2*)psi, (double2*)lam, W, (int)B, pg, pg_one_bits(pg), (const double*)mats,
                                    p->n_shared_mats[1], p->n_ps_mats[1], part, nch);
             else
                 hipLaunchKernelGGL(k_pg_adj<float2>, dim3((unsigned)nch, (unsigned)B), dim3(256), 0, s, psi,
-                                   lam, W, (int)B, pg, (const float*)mats, p->n_shared_mats[1],
+                                   lam, W, (int)B, pg, pg_one_bits(pg), (const float*)mats, p->n_shared_mats[1],
                                    p->n_ps_mats[1], part, nch);
             prof_end(p, s, ev, K_PG_ADJ, 4.0 * (double)amp_size(p) * touched * amps, p->pg_bwd_flops[i] * amps,
                      kPgSub0 + pg_prof_class(pg));
@@ -2992,7 +3082,8 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
         hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)n_out), dim3(256), 0, s,
                            (const double*)part, T->grad_csr, p->n_weights, p->n_inputs, (int)B,
                            (const int64_t*)T->pu, (const int32_t*)T->nchv, gw, gx, w,
-                           (int)p->opts.weight_remap);
+                           (int)p->opts.weight_remap,
+                           p->opts.method == QSV_METHOD_PER_GATE && !p->multi ? nch : int64_t(0));
         prof_end(p, s, ev, K_GRAD_REDUCE, 8.0 * (double)std::max<int64_t>(p->pu_total, 1) * B, 0.0);
     }
     HIP_TRY(hipGetLastError());
