@@ -120,10 +120,23 @@ struct DTerm {
 };
 
 struct DStage {
-    int32_t reg[kRegBits];  // local tile bits held in registers, position p -> local bit
+    int32_t reg[kRegBits];  // local tile bits held in registers, position p -> local bit (ascending)
     int32_t op0, op1;       // ops [op0, op1)
-    int32_t pad[2];
+    int32_t sb[kRegBits];   // swizzled LDS byte offset of each register bit
+    int32_t ex;             // table-driven kernels: how the tile is re-laid out before the stage
+    int32_t pad;
 };
+
+// Re-layout through LDS (DStage.ex, DPass.nat.ex)
+enum : int32_t {
+    EX_MOVE = 1,   // the layout changes
+    EX_CROSS = 2,  // waves read what other waves wrote: barriers
+    EX_LEAD = 4    // and one before, since the last re-layout stayed within waves
+};
+
+// Bank-conflict swizzle of a tile-local amplitude index: a bijection on [0, 2^m),
+// linear over XOR.
+inline int swizzle(int l) { return l ^ (((l >> 5) ^ (l >> 10)) & 31); }
 
 enum PassFlags : int32_t {
     PF_FIRST_BWD = 1,  // backward: read psi_N from the caller's state, build lambda on the fly
@@ -140,6 +153,8 @@ struct DPass {
     int32_t gout0;        // backward: first gradient output (DGOut) of this pass
     int32_t n_gout;       // backward: gradient outputs of this pass
     int32_t pad;
+    DStage nat;           // layout of loads and stores (no ops); ex: what storing needs at the end
+    int32_t nat_gr[kRegBits];  // its register bits as amplitude-index values
     int32_t lq[kMaxQ];    // local tile bit j -> global bit shift (W-1-qubit), j < m
     int32_t oq[kMaxQ];    // tile-index bit k -> global bit shift, k < W-m
 };

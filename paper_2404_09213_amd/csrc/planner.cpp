@@ -871,6 +871,40 @@ struct PassBuilder {
     // qubits does not change under a unitary applied to both states on them.
     std::vector<int> first_on;
 
+    // The table-driven kernels' layouts: registers of the load / store layout
+    // (bit 0 when it is amplitude bit 0, for 16-byte accesses, and the top bits),
+    // LDS offsets, and what each change of layout needs. Thread-index bits are
+    // the other local bits, ascending: two layouts with the same bits on the wave
+    // index exchange amplitudes within waves only.
+    void lay_out(DPass& ps, int m) {
+        const int top[kRegBits] = {ps.lq[0] == 0 ? 0 : m - 4, m - 3, m - 2, m - 1};
+        std::copy(top, top + kRegBits, ps.nat.reg);
+        auto waves = [&](const int32_t* reg) {
+            uint32_t w = 0;
+            for (int j = m - 1, n = std::max(0, m - kRegBits - 6); n > 0; --j)
+                if (std::find(reg, reg + kRegBits, j) == reg + kRegBits) {
+                    w |= 1u << j;
+                    --n;
+                }
+            return w;
+        };
+        const int32_t* cur = ps.nat.reg;
+        bool own = false;
+        auto change = [&](DStage& to) {
+            for (int i = 0; i < kRegBits; ++i) to.sb[i] = swizzle(1 << to.reg[i]) * 8;
+            to.ex = 0;
+            if (!std::equal(cur, cur + kRegBits, to.reg)) {
+                const bool cross = waves(cur) != waves(to.reg);
+                to.ex = EX_MOVE | (cross ? EX_CROSS : 0) | (cross && own ? EX_LEAD : 0);
+                own = !cross;
+            }
+            cur = to.reg;
+        };
+        for (int s = 0; s < ps.n_stages; ++s) change(p->stages[ps.stage0 + s]);
+        change(ps.nat);
+        for (int i = 0; i < kRegBits; ++i) ps.nat_gr[i] = 1 << ps.lq[ps.nat.reg[i]];
+    }
+
     void build(const std::vector<int>& gates, uint32_t dense, int m, int c, int flags,
                std::vector<DPass>& out, std::vector<int32_t>& order) {
         const int W = p->W;
@@ -1245,6 +1279,7 @@ struct PassBuilder {
             p->stages.push_back(st);
         }
         for (auto& v : wait.vecs) p->ops[v.op].mat = add_factors(p, v.f);
+        lay_out(ps, m);
         ps.n_gslots = nslot;
         ps.n_gout = (int32_t)p->gouts.size() - ps.gout0;
         out.push_back(ps);
