@@ -92,6 +92,8 @@ enum OpKind : int32_t {
     OP_DVEC = 11,  // multiply register k by complex entry k & pos of 4 slots from `mat`, where it
                    // is not 1 (k has a bit of the mask `pos`)
 };
+// table-driven backward: components only, nothing is applied
+constexpr int32_t OP_NONE = 13;
 inline bool is_grad_op(int kind) { return kind >= OP_GX && kind <= OP_GZ; }
 
 // Control encoding: ctl = -1 none; 0..3 register position; 0x100 | shift for
@@ -108,7 +110,8 @@ struct DOp {
     int32_t term0;    // OP_SIGN: first term
     int32_t nterm;    // OP_SIGN: number of terms; uniform 16-bit mask in `pos`
     int32_t ctl2;     // second control, same encoding (-1 none)
-    int32_t pad;
+    int32_t comps;    // table-driven backward: components (bit 0 X, 1 Y, 2 Z) taken before the op
+                      // is applied, in consecutive slots from `slot` on
 };
 
 // Sign term of an OP_SIGN group, for one stage layout: if every listed bit

@@ -1184,23 +1184,26 @@ struct PassBuilder {
                             break;
                         }
                 sign_op = -1;
-                auto comp_op = [&](int kind) {
-                    DOp o;
-                    std::memset(&o, 0, sizeof o);
-                    o.kind = kind;
-                    o.pos = pos_of(U.qubit);
-                    o.sh = W - 1 - U.qubit;
-                    o.ctl = o.ctl2 = -1;
-                    o.slot = nslot++;
-                    p->ops.push_back(o);
-                    return o.slot;
-                };
+                // the unit's op; a table-driven backward takes its components (X, Y, Z
+                // in consecutive slots) in the same op, before applying it
+                DOp o;
+                std::memset(&o, 0, sizeof o);
+                o.pos = pos_of(U.qubit);
+                o.sh = W - 1 - U.qubit;
+                o.ctl = o.ctl2 = -1;
+                o.slot = -1;
+                if (is_multi(G.kind) && U.gates.size() == 1) {
+                    o.ctl = ctl_code(G.q0);
+                    if (n_ctl(G.kind) == 2) o.ctl2 = ctl_code(G.q1);
+                }
                 if (backward && U.comps) {
                     // chain: X/Y/Z components after the chain, one output per
                     // parametric gate, then the chain's product uncomputed at once
                     int slot_of[3] = {-1, -1, -1};
+                    o.comps = U.comps;
+                    o.slot = nslot;
                     for (int a = 0; a < 3; ++a)
-                        if (U.comps >> a & 1) slot_of[a] = comp_op(OP_GX + a);
+                        if (U.comps >> a & 1) slot_of[a] = nslot++;
                     const int n = (int)U.gates.size();
                     for (int j = 0; j < n; ++j) {
                         const qsv_gate& Gj = p->gates[U.gates[j]];
@@ -1226,43 +1229,30 @@ struct PassBuilder {
                     // gradient partial (before uncomputing the gate), then U^dagger
                     const int g = U.gates[0];
                     if (G.src != QSV_SRC_NONE) {
-                        DOp o;
-                        std::memset(&o, 0, sizeof o);
-                        o.kind = (G.kind == QSV_RY || G.kind == QSV_CRY)   ? OP_GY
-                                 : (G.kind == QSV_RZ || G.kind == QSV_CRZ) ? OP_GZ
-                                                                           : OP_GX;
-                        o.pos = pos_of(U.qubit);
-                        o.sh = W - 1 - U.qubit;
-                        o.ctl = o.ctl2 = -1;
-                        if (is_multi(G.kind)) {
-                            o.ctl = ctl_code(G.q0);
-                            if (n_ctl(G.kind) == 2) o.ctl2 = ctl_code(G.q1);
+                        const int axis = axis_of(G.kind == QSV_CRY ? QSV_RY : G.kind == QSV_CRZ ? QSV_RZ : G.kind);
+                        int slot;
+                        if (cores) {
+                            slot = comp(U, OP_GX + axis, o.ctl, o.ctl2);
+                        } else {
+                            o.comps = 1 << axis;
+                            slot = o.slot = nslot++;
                         }
-                        o.mat = 0;
-                        o.slot = nslot++;
-                        p->ops.push_back(o);
                         DGOut go;
                         std::memset(&go, 0, sizeof go);
                         go.ord = p->param_ordinal[g];
                         go.axis = -1;
-                        go.c0 = o.slot;
+                        go.c0 = slot;
                         go.c1 = go.c2 = -1;
                         p->gouts.push_back(go);
                     }
                 }
-                if (starts_timelines()) continue;
-                DOp o;
-                std::memset(&o, 0, sizeof o);
+                if (starts_timelines()) {
+                    o.kind = OP_NONE;
+                    if (o.comps) p->ops.push_back(o);
+                    continue;
+                }
                 o.kind = recipe_class(p, U.gates);
                 o.mat = add_recipe(p, U.gates, backward);
-                o.pos = pos_of(U.qubit);
-                o.sh = W - 1 - U.qubit;
-                o.ctl = o.ctl2 = -1;
-                o.slot = -1;
-                if (is_multi(G.kind) && U.gates.size() == 1) {
-                    o.ctl = ctl_code(G.q0);
-                    if (n_ctl(G.kind) == 2) o.ctl2 = ctl_code(G.q1);
-                }
                 p->ops.push_back(o);
             }
             if (cores) {
@@ -1309,6 +1299,11 @@ double pass_flops(const qsv_plan_t* p, const DPass& ps, bool backward) {
             const DOp& op = p->ops[o];
             const bool grad = is_grad_op(op.kind);
             f += op_flops(op) * (backward && !grad ? 2.0 : 1.0);
+            DOp c = op;  // components taken by the same op
+            for (int a = 0; a < 3; ++a) {
+                c.kind = OP_GX + a;
+                if (op.comps >> a & 1) f += op_flops(c);
+            }
         }
     return f;
 }
@@ -1613,7 +1608,7 @@ int build_multi(qsv_plan_t* p, const std::vector<CircuitIn>& cs) {
         }
         for (int oi = 0; oi < (int)sub.ops.size(); ++oi) {
             DOp o = sub.ops[oi];
-            if (o.kind != OP_SIGN && o.kind != OP_SWAP && !is_grad_op(o.kind)) o.mat = fix_mat(o.mat, oi >= bwd_op0);
+            if (o.kind != OP_SIGN && o.kind != OP_SWAP && o.kind != OP_NONE && !is_grad_op(o.kind)) o.mat = fix_mat(o.mat, oi >= bwd_op0);
             if (o.kind == OP_SIGN) o.term0 += t0;
             p->ops.push_back(o);
         }

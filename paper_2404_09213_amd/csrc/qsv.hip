@@ -165,6 +165,28 @@ __device__ __forceinline__ float row_sum(float v) {
     return v;
 }
 
+// Row sums of four values at once: the lanes of bank 0, 1, 2, 3 of a row (lane
+// bits 2 and 3) end with the row's total of a, b, c, d. A bank mask keeps one
+// value in half of the banks while the other half takes the next value. Two
+// wait states lie between a write and a DPP read of it.
+__device__ __forceinline__ float row_sum4(float a, float b, float c, float d) {
+    __asm__ volatile(
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %3, %3 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+        : "+&v"(a), "+&v"(b) : "v"(c), "v"(d));
+    return a;
+}
+
 __device__ __forceinline__ float im_conj_mul(float2 l, float2 p) { return l.x * p.y - l.y * p.x; }
 __device__ __forceinline__ float re_conj_mul(float2 l, float2 p) { return l.x * p.x + l.y * p.y; }
 __device__ __forceinline__ double im_conj_mul(double2 l, double2 p) { return l.x * p.y - l.y * p.x; }
@@ -1318,7 +1340,7 @@ __device__ __forceinline__ float r_gx(const float2 (&ps)[kRegs], const float2 (&
     }
     return acc;
 }
-template <int P>
+template <int P, bool CTL>
 __device__ __forceinline__ float r_gy(const float2 (&ps)[kRegs], const float2 (&lm)[kRegs], int cm) {
     float acc = 0.f;
 #pragma unroll
@@ -1326,17 +1348,17 @@ __device__ __forceinline__ float r_gy(const float2 (&ps)[kRegs], const float2 (&
         if (k & (1 << P)) continue;
         const int k1 = k | (1 << P);
         const float v = re_conj_mul(lm[k1], ps[k]) - re_conj_mul(lm[k], ps[k1]);
-        acc += ((cm >> k) & 1) ? v : 0.f;
+        acc += (!CTL || ((cm >> k) & 1)) ? v : 0.f;
     }
     return acc;
 }
-template <int P>
+template <int P, bool CTL>
 __device__ __forceinline__ float r_gz(const float2 (&ps)[kRegs], const float2 (&lm)[kRegs], int cm) {
     float acc = 0.f;
 #pragma unroll
     for (int k = 0; k < kRegs; ++k) {
         const float v = im_conj_mul(lm[k], ps[k]);
-        acc += ((cm >> k) & 1) ? ((k & (1 << P)) ? -v : v) : 0.f;
+        acc += (!CTL || ((cm >> k) & 1)) ? ((k & (1 << P)) ? -v : v) : 0.f;
     }
     return acc;
 }
@@ -1442,30 +1464,31 @@ __device__ __forceinline__ void apply_op(const DOp& op, float2 (&a)[kRegs], floa
 #undef BOTH_
 }
 
-__device__ __forceinline__ float grad_op(const DOp& op, const float2 (&ps)[kRegs],
-                                         const float2 (&lm)[kRegs], int gT) {
-    float v = 0.f;
+// The components of an op, Im<l|X|psi>, Im<l|Y|psi>, Im<l|Z|psi> of its qubit
+// (only those with their bit in op.comps) over this thread's amplitudes.
+template <int P, bool CTL>
+__device__ __forceinline__ void r_comps(const float2 (&ps)[kRegs], const float2 (&lm)[kRegs], int cm, int comps,
+                                        float (&g)[3]) {
+    if (comps & 1) g[0] = r_gx<P, CTL>(ps, lm, cm);
+    if (comps & 2) g[1] = r_gy<P, CTL>(ps, lm, cm);
+    if (comps & 4) g[2] = r_gz<P, CTL>(ps, lm, cm);
+}
+__device__ __forceinline__ void grad_op(const DOp& op, const float2 (&ps)[kRegs], const float2 (&lm)[kRegs], int gT,
+                                        float (&g)[3]) {
     const bool ctl = op.ctl >= 0;
     const int cm = ctl_mask(op.ctl, gT) & ctl_mask(op.ctl2, gT);
-    if (op.kind == OP_GX) {
-#define C_(P) v = ctl ? r_gx<P, true>(ps, lm, cm) : r_gx<P, false>(ps, lm, cm)
-        QSV_DISPATCH_POS(op.pos, C_)
-#undef C_
-    } else if (op.kind == OP_GY) {
-#define C_(P) v = r_gy<P>(ps, lm, cm)
-        QSV_DISPATCH_POS(op.pos, C_)
-#undef C_
-    } else {
-        if (op.pos >= 0) {
-#define C_(P) v = r_gz<P>(ps, lm, cm)
-            QSV_DISPATCH_POS(op.pos, C_)
-#undef C_
-        } else {
-            v = r_gz_all(ps, lm, cm);
-            if ((gT >> op.sh) & 1) v = -v;
-        }
+    if (op.pos < 0) {  // Z on a qubit outside the registers
+        const float v = r_gz_all(ps, lm, cm);
+        g[2] = ((gT >> op.sh) & 1) ? -v : v;
+        return;
     }
-    return v;
+#define C_(P)                                                   \
+    do {                                                        \
+        if (ctl) r_comps<P, true>(ps, lm, cm, op.comps, g);     \
+        else r_comps<P, false>(ps, lm, cm, op.comps, g);        \
+    } while (0)
+    QSV_DISPATCH_POS(op.pos, C_)
+#undef C_
 }
 
 __device__ __forceinline__ int tile_base_of(const DPass* __restrict__ P, int tbits, int64_t tis) {
@@ -1480,7 +1503,7 @@ __device__ __forceinline__ int tile_base_of(const DPass* __restrict__ P, int tbi
 __device__ __forceinline__ M2 op_matrix(const DOp& op, const float* __restrict__ mats, int b, int n_shared,
                                         int n_ps) {
     M2 M{};
-    if (op.kind != OP_SIGN && op.kind != OP_SWAP && op.kind < OP_GX)
+    if (op.kind < OP_SIGN)
         M = load_m2(mat_ptr(mats, op.mat, b, n_shared, n_ps));
     return M;
 }
@@ -1664,12 +1687,25 @@ __device__ __forceinline__ void pass_bwd_tile(
                     nop = O[oi + 1];
                     nM = op_matrix(nop, mats, b, n_shared, n_ps);
                 }
-                if (op.kind >= OP_GX) {
-                    // every lane of a row stores the row's sum (same value, same address)
-                    red[(wave * 4 + (lane >> 4)) * ng + op.slot] = row_sum(grad_op(op, ps, lm, L.gT));
-                } else {
-                    apply_op<2>(op, ps, lm, M, L.gT, Tm);
+                if (op.comps) {
+                    // components first: a gate run costs one dispatch for its up to three
+                    // components and its uncompute (one each before)
+                    float g[3] = {0.f, 0.f, 0.f};
+                    grad_op(op, ps, lm, L.gT, g);
+                    float* const r = red + (wave * 4 + (lane >> 4)) * ng + op.slot;
+                    if ((op.comps & (op.comps - 1)) == 0) {
+                        // every lane of a row stores the row's sum (same value, same address)
+                        *r = row_sum(g[0] + g[1] + g[2]);
+                    } else {
+                        // bank i of the row holds the i-th component taken
+                        const int bank = (lane >> 2) & 3, n = __builtin_popcount(op.comps);
+                        const float x = op.comps & 1 ? g[0] : g[1], z = g[2];
+                        const float y = (op.comps & 3) == 3 ? g[1] : z;
+                        const float v = row_sum4(x, y, z, 0.f);
+                        if (bank < n) r[bank] = v;
+                    }
                 }
+                apply_op<2>(op, ps, lm, M, L.gT, Tm);
                 op = nop;
                 M = nM;
             }
