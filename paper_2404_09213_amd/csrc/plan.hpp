@@ -145,6 +145,7 @@ enum PassFlags : int32_t {
     PF_FIRST_BWD = 1,  // backward: read psi_N from the caller's state, build lambda on the fly
     PF_LAST_BWD = 2,   // backward: nothing is written back
     PF_INIT_FWD = 4,   // forward: generate the product-state init instead of loading
+    PF_LAST_FWD = 8,   // forward: the state is final (a table-driven pass can take the readout along)
 };
 
 struct DPass {

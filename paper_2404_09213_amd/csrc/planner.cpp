@@ -1504,7 +1504,8 @@ int build_schedule(qsv_plan_t* p) {
         if (!covers(passes, body.size())) return QSV_ERR_GATE;
         PassBuilder pb{p, false, {}};
         for (size_t i = 0; i < passes.size(); ++i)
-            pb.build(passes[i], dense[i], m, c, i == 0 ? PF_INIT_FWD : 0, p->fwd_pass, p->fwd_order);
+            pb.build(passes[i], dense[i], m, c, (i == 0 ? PF_INIT_FWD : 0) | (i + 1 == passes.size() ? PF_LAST_FWD : 0),
+                     p->fwd_pass, p->fwd_order);
     }
     {
         std::vector<uint32_t> dense;

@@ -145,10 +145,26 @@ __device__ __forceinline__ void store_pair(double2* p, bool vec, double2 a, doub
     (void)vec;
 }
 
+// float64 sum over a wave, every lane gets the total: DPP lane moves (pairs,
+// quads, half rows, rows, then row 0 -> 1, 2 -> 3 and rows 0-1 -> 2-3
+// broadcasts), lane 63 holds the total. All lanes must be active.
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ double dpp_d(double v) {
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWMASK, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, ROWMASK, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp_d<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
+    v += dpp_d<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
+    v += dpp_d<0x141, 0xF>(v);  // row_half_mirror
+    v += dpp_d<0x140, 0xF>(v);  // row_mirror
+    v += dpp_d<0x142, 0xA>(v);  // row_bcast:15 into rows 1, 3
+    v += dpp_d<0x143, 0xC>(v);  // row_bcast:31 into rows 2, 3
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)x, 63), hi = __builtin_amdgcn_readlane((int)(x >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
 // float32 sum over the 16 lanes of a DPP row (pairs, quads, half rows, rows);
@@ -540,35 +556,36 @@ __global__ __launch_bounds__(256) void k_expval_part(const V* __restrict__ state
 
 __global__ __launch_bounds__(256) void k_expval_final(const double* __restrict__ part, int W,
                                                       int64_t nchunk, double* __restrict__ out) {
-    __shared__ double red[256];
+    __shared__ double red[4];
     const int b = blockIdx.y, i = blockIdx.x, t = threadIdx.x;
     double s = 0.0;
     for (int64_t c = t; c < nchunk; c += 256) s += part[((size_t)b * nchunk + c) * W + i];
-    red[t] = s;
+    s = wave_sum(s);
+    if ((t & 63) == 0) red[t >> 6] = s;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    if (t == 0) out[(size_t)b * W + i] = red[0];
+    if (t == 0) out[(size_t)b * W + i] = red[0] + red[1] + red[2] + red[3];
 }
 
 // ----------------------------------------------------------------------------
 // gradient reduction: partials[(ordinal * B + b) * nch + chunk]
 // ----------------------------------------------------------------------------
 // Partial of ordinal o, sample b, chunk k at part[B * pu[o] + b * nch[o] + k];
-// with nch1 > 0 every ordinal has nch1 chunks instead.
+// with nch1 > 0 every ordinal has nch1 chunks instead. NT threads sum one
+// output: a block where outputs have many partials, a wave where they have few
+// (the 512-circuit set, 26,471 weights of at most 64 partials: 37 -> REDUCE_US us).
+template <int NT>
 __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ part,
                                                      const int32_t* __restrict__ csr, int n_weights,
-                                                     int n_inputs, int B,
+                                                     int n_inputs, int n_out, int B,
                                                      const int64_t* __restrict__ pu,
                                                      const int32_t* __restrict__ nchv,
                                                      double* __restrict__ gw,
                                                      double* __restrict__ gx,
                                                      const float* __restrict__ weights, int remap, int64_t nch1) {
-    __shared__ double red[256];
-    const int t = threadIdx.x;
-    const int o = blockIdx.x;  // output index: weights first, then (b, input)
+    __shared__ double red[4];
+    const int t = threadIdx.x % NT;
+    const int o = blockIdx.x * (256 / NT) + threadIdx.x / NT;  // output index: weights first, then (b, input)
+    if (o >= n_out) return;  // whole waves, and only in the last block of the wave variant
     double s = 0.0;
     int j, b0, b1;
     const int32_t* list;
@@ -590,17 +607,17 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ 
         b1 = b + 1;
     }
     for (int l = 0; l < nl; ++l) {
-        const int o = list[l];
-        const int64_t nch = nch1 > 0 ? nch1 : nchv[o];
+        const int q = list[l];
+        const int64_t nch = nch1 > 0 ? nch1 : nchv[q];
         const int64_t per = (int64_t)(b1 - b0) * nch;
-        const double* base = part + (int64_t)B * (nch1 > 0 ? o * nch1 : pu[o]) + (int64_t)b0 * nch;
-        for (int64_t e = t; e < per; e += 256) s += base[e];
+        const double* base = part + (int64_t)B * (nch1 > 0 ? q * nch1 : pu[q]) + (int64_t)b0 * nch;
+        for (int64_t e = t; e < per; e += NT) s += base[e];
     }
-    red[t] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
+    s = wave_sum(s);
+    if (NT == 256) {
+        if ((t & 63) == 0) red[t >> 6] = s;
         __syncthreads();
+        s = red[0] + red[1] + red[2] + red[3];
     }
     if (t == 0) {
         if (o < n_weights) {
@@ -609,9 +626,9 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ 
                 const double th = tanh((double)weights[j]);
                 f = M_PI * (1.0 - th * th);
             }
-            gw[j] = red[0] * f;
+            gw[j] = s * f;
         }
-        else if (gx) gx[(size_t)b0 * n_inputs + j] = red[0];
+        else if (gx) gx[(size_t)b0 * n_inputs + j] = s;
     }
 }
 
@@ -1302,20 +1319,21 @@ __device__ __forceinline__ void r_swap(float2 (&a)[kRegs], int cm) {
 }
 
 // diagonal ops apply to the registers in cm (the controls' mask; 0xFFFF = all)
-template <int P>
+template <int P, bool CTL>
 __device__ __forceinline__ void r_diag(float2 (&a)[kRegs], const M2& M, int cm) {
 #pragma unroll
     for (int k = 0; k < kRegs; ++k) {
         const float2 u = cmul((k & (1 << P)) ? M.m11 : M.m00, a[k]);
-        a[k] = ((cm >> k) & 1) ? u : a[k];
+        a[k] = !CTL || ((cm >> k) & 1) ? u : a[k];
     }
 }
 
+template <bool CTL>
 __device__ __forceinline__ void r_phase_all(float2 (&a)[kRegs], float2 ph, int cm) {
 #pragma unroll
     for (int k = 0; k < kRegs; ++k) {
         const float2 u = cmul(ph, a[k]);
-        a[k] = ((cm >> k) & 1) ? u : a[k];
+        a[k] = !CTL || ((cm >> k) & 1) ? u : a[k];
     }
 }
 
@@ -1434,14 +1452,14 @@ __device__ __forceinline__ void apply_op(const DOp& op, float2 (&a)[kRegs], floa
         break;
     case OP_DIAG:
         if (op.pos >= 0) {
-#define U_(x) r_diag<P_>(x, M, cm)
+#define U_(x) if (ctl) r_diag<P_, true>(x, M, cm); else r_diag<P_, false>(x, M, cm)
 #define C_(P) { constexpr int P_ = P; BOTH_(U_); }
             QSV_DISPATCH_POS(op.pos, C_)
 #undef C_
 #undef U_
         } else {
             const float2 ph = ((gT >> op.sh) & 1) ? M.m11 : M.m00;
-#define U_(x) r_phase_all(x, ph, cm)
+#define U_(x) if (ctl) r_phase_all<true>(x, ph, cm); else r_phase_all<false>(x, ph, cm)
             BOTH_(U_);
 #undef U_
         }
@@ -1497,6 +1515,53 @@ __device__ __forceinline__ int tile_base_of(const DPass* __restrict__ P, int tbi
     return base;
 }
 
+// <Z_i> partials of a tile whose final amplitudes are in the registers of the
+// load / store layout: out[i] = sum |a|^2 (1 - 2 bit_i) over the tile, float32
+// per thread (16 amplitudes), float64 above. Saves reading the state again (the
+// 512-circuit set, 195 MB: 65 -> READOUT_US us). lds: 52 doubles.
+__device__ __forceinline__ void tile_readout(const DPass* __restrict__ P, const Lay& L, const float2 (&a)[kRegs],
+                                             bool act, int W, int base, double* lds, double* __restrict__ out) {
+    const int t = threadIdx.x, m = P->m, nv = 1 + m;  // total, 4 register bits, m - 4 thread bits
+    float T = 0.f, S[kRegBits] = {0.f, 0.f, 0.f, 0.f};
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < kRegs; ++k) {
+            const float p = a[k].x * a[k].x + a[k].y * a[k].y;
+            T += p;
+#pragma unroll
+            for (int r = 0; r < kRegBits; ++r)
+                if (k >> r & 1) S[r] += p;
+        }
+    }
+    __syncthreads();  // the last re-layout's reads
+#pragma unroll
+    for (int v = 0; v < 13; ++v) {
+        if (v >= nv) continue;
+        const double x = v == 0 ? (double)T : v <= kRegBits ? (double)S[(v - 1) & 3] : ((t >> (v - 5)) & 1) ? (double)T : 0.0;
+        const double r = wave_sum(x);
+        if ((t & 63) == 0) lds[(t >> 6) * 13 + v] = r;
+    }
+    __syncthreads();
+    if (t < W) {
+        const int nw = (int)(blockDim.x >> 6), sh = W - 1 - t;
+        auto tot = [&](int v) {
+            double s = 0.0;
+            for (int w = 0; w < nw; ++w) s += lds[w * 13 + v];
+            return s;
+        };
+        int v = 0, i = 0;  // reduced value of this qubit's bit, 0: outside the tile
+        for (int j = 0; j < m; ++j) {
+            int r = -1;
+            for (int p = 0; p < kRegBits; ++p)
+                if (P->nat.reg[p] == j) r = p;
+            if (P->lq[j] == sh) v = r >= 0 ? 1 + r : 5 + i;
+            if (r < 0) ++i;
+        }
+        const double e = tot(0);
+        out[t] = v ? e - 2.0 * tot(v) : ((base >> sh) & 1) ? -e : e;
+    }
+}
+
 // One fused forward pass over one tile of one sample. st: the sample's 2^W
 // amplitudes; tis: tile index within the sample; lds: 2^m float2.
 // An op's 2x2 matrix (ops without one get zeros).
@@ -1515,7 +1580,7 @@ __device__ __forceinline__ void pass_fwd_tile(const DPass* __restrict__ P,
                                               const float* __restrict__ mats, int n_shared,
                                               int n_ps, const int32_t* __restrict__ pm,
                                               float2* __restrict__ st, int W, int b, int64_t tis,
-                                              float2* lds) {
+                                              float2* lds, double* __restrict__ epart) {
     const int m = P->m;
     const int t = threadIdx.x;
     const bool act = t < (1 << (m - kRegBits));
@@ -1566,6 +1631,7 @@ __device__ __forceinline__ void pass_fwd_tile(const DPass* __restrict__ P,
     }
     relay(P->nat);
     if (act) g_store(st, P, L, a);
+    if (epart && (P->flags & PF_LAST_FWD)) tile_readout(P, L, a, act, W, base, (double*)lds, epart);
 }
 
 // One fused backward pass over one tile of one sample. psiN_s / psi_s / lam_s:
@@ -1753,7 +1819,7 @@ __global__ __launch_bounds__(1024) void k_pass_fwd(const DPass* __restrict__ P,
     const int64_t tile = blockIdx.x;
     const int b = (int)(tile >> tbits);
     const int64_t tis = tile & ((int64_t(1) << tbits) - 1);
-    pass_fwd_tile(P, S, O, Tm, mats, n_shared, n_ps, pm, state + ((size_t)b << W), W, b, tis, lds);
+    pass_fwd_tile(P, S, O, Tm, mats, n_shared, n_ps, pm, state + ((size_t)b << W), W, b, tis, lds, nullptr);
 }
 
 __global__ __launch_bounds__(256) void k_pass_bwd(
@@ -1783,7 +1849,8 @@ __global__ __launch_bounds__(256) void k_multi_fwd(
     const DCirc* __restrict__ C, const DItem* __restrict__ Q,
     const DPass* __restrict__ passes, const DStage* __restrict__ S, const DOp* __restrict__ O,
     const DTerm* __restrict__ Tm, const float* __restrict__ mats, int n_shared, int n_ps,
-    const int32_t* __restrict__ pm, float2* __restrict__ state, int64_t row) {
+    const int32_t* __restrict__ pm, float2* __restrict__ state, int64_t row, double* __restrict__ epart,
+    int64_t nchunk_tot) {
     extern __shared__ float2 lds[];
     const DItem I = Q[blockIdx.x];
     const DCirc& c = C[I.c];
@@ -1791,7 +1858,8 @@ __global__ __launch_bounds__(256) void k_multi_fwd(
     const int b = I.tile >> tbits;
     const int64_t tis = I.tile & ((1 << tbits) - 1);
     pass_fwd_tile(passes + c.fwd0 + I.pass, S, O, Tm, mats, n_shared, n_ps, pm + c.pm0,
-                  state + (size_t)b * row + c.amp0, c.W, b, tis, lds);
+                  state + (size_t)b * row + c.amp0, c.W, b, tis, lds,
+                  epart ? epart + ((size_t)b * nchunk_tot + c.ic0 + tis) * 32 : nullptr);
 }
 
 __global__ __launch_bounds__(256) void k_multi_bwd(
@@ -1897,12 +1965,38 @@ __global__ __launch_bounds__(256) void k_expval_part_multi(const DCirc* __restri
     }
 }
 
+// The same over the tiles of each circuit's last forward pass, whose partials
+// that pass can also write itself, bit for bit the same (see fused_readout).
+__global__ __launch_bounds__(256) void k_expval_tiles_multi(const DCirc* __restrict__ C, int n_circ,
+                                                            const DPass* __restrict__ passes,
+                                                            const float2* __restrict__ state, int64_t row,
+                                                            int64_t nchunk_tot, double* __restrict__ part) {
+    __shared__ double red[4 * 13];
+    int lo = 0, hi = n_circ - 1;
+    const int x = blockIdx.x;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (C[mid].ic0 <= x) lo = mid; else hi = mid - 1;
+    }
+    const DCirc& c = C[lo];
+    const DPass* P = passes + c.fwd0 + c.n_fwd - 1;
+    const int tbits = c.W - c.m, t = threadIdx.x, b = blockIdx.y;
+    const int base = tile_base_of(P, tbits, x - c.ic0);
+    const bool act = t < (1 << (c.m - kRegBits));
+    const Lay L = lay_of(P, P->nat.reg, t, base, tbits);
+    float2 a[kRegs];
+#pragma unroll
+    for (int k = 0; k < kRegs; ++k) a[k] = make_float2(0.f, 0.f);
+    if (act) g_load(state + (size_t)b * row + c.amp0, P, L, a);
+    tile_readout(P, L, a, act, c.W, base, red, part + ((size_t)b * nchunk_tot + x) * 32);
+}
+
 // E[b, e0_c + i] = sum over circuit c's chunks; grid (total qubits, B)
 __global__ __launch_bounds__(256) void k_expval_final_multi(const DCirc* __restrict__ C, int n_circ,
                                                             const double* __restrict__ part,
                                                             int64_t nchunk_tot, int Wtot,
                                                             double* __restrict__ out) {
-    __shared__ double red[256];
+    __shared__ double red[4];
     int lo = 0, hi = n_circ - 1;
     const int col = blockIdx.x;
     while (lo < hi) {
@@ -1914,13 +2008,10 @@ __global__ __launch_bounds__(256) void k_expval_final_multi(const DCirc* __restr
     const int b = blockIdx.y, t = threadIdx.x;
     double s = 0.0;
     for (int64_t k = t; k < c.nchunk; k += 256) s += part[((size_t)b * nchunk_tot + c.ic0 + k) * 32 + i];
-    red[t] = s;
+    s = wave_sum(s);
+    if ((t & 63) == 0) red[t >> 6] = s;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    if (t == 0) out[(size_t)b * Wtot + col] = red[0];
+    if (t == 0) out[(size_t)b * Wtot + col] = red[0] + red[1] + red[2] + red[3];
 }
 
 // ----------------------------------------------------------------------------
@@ -2728,8 +2819,15 @@ size_t qsv_workspace_size(const qsv_plan_t* p, int64_t B, int32_t op) {
 
 // true when the last generated forward kernel can write the readout partials
 // itself: fused method, generated kernels, at least one pass
+// (generated), or the table-driven passes of a multi-circuit plan can: every
+// circuit has a pass, and its tiles are the readout's chunks
 static bool fused_readout(const qsv_plan_t* p, const DeviceTables* T) {
-    return !p->multi && p->opts.method != QSV_METHOD_PER_GATE && !T->fwd_fn.empty() && !p->fwd_pass.empty();
+    if (p->multi) {
+        for (const DCirc& c : p->circ)
+            if (!c.n_fwd || c.m != std::min(c.W, 12)) return false;
+        return true;
+    }
+    return p->opts.method != QSV_METHOD_PER_GATE && !T->fwd_fn.empty() && !p->fwd_pass.empty();
 }
 
 // Forward over validated arguments. epart (used only when fused_readout())
@@ -2770,7 +2868,8 @@ static int forward_impl(const qsv_plan_t* p, const float* w, const float* x, int
             hipLaunchKernelGGL(k_multi_fwd, dim3((unsigned)n), dim3(256), (size_t)8 << kMaxTileQubitsTables, s,
                                (const DCirc*)T->circ, (const DItem*)(Q->fwd + i0), (const DPass*)T->fwd_pass,
                                (const DStage*)T->stages, (const DOp*)T->ops, (const DTerm*)T->terms,
-                               (const float*)mats, p->n_shared_mats[0], p->n_ps_mats[0], T->prefix_mat, st, p->row);
+                               (const float*)mats, p->n_shared_mats[0], p->n_ps_mats[0], T->prefix_mat, st, p->row,
+                               epart, p->nchunk_tot);
         }
         prof_end(p, s, ev, K_MULTI_FWD, bytes, flops);
         HIP_TRY(hipGetLastError());
@@ -2879,6 +2978,17 @@ static size_t readout_bytes(const qsv_plan_t* p, int64_t B) {
                                    sizeof(double)));
 }
 
+// expectations of a multi-circuit plan from its readout partials
+static int expval_final_multi(const qsv_plan_t* p, const DeviceTables* T, const double* part, int64_t B, double* out,
+                              hipStream_t s) {
+    hipEvent_t ev = prof_begin(p, s);
+    hipLaunchKernelGGL(k_expval_final_multi, dim3((unsigned)p->Wtot, (unsigned)B), dim3(256), 0, s,
+                       (const DCirc*)T->circ, (int)p->circ.size(), part, p->nchunk_tot, p->Wtot, out);
+    prof_end(p, s, ev, K_EXPVAL_FINAL, 8.0 * (double)B * p->nchunk_tot * 32, 0.0);
+    HIP_TRY(hipGetLastError());
+    return QSV_OK;
+}
+
 // qsv_forward_expval with its workspace split by the caller: matrices in ws,
 // readout partials behind the first mats_sz bytes
 static int forward_expval_impl(const qsv_plan_t* p, const float* w, const float* x, int64_t B, void* d_state,
@@ -2894,8 +3004,13 @@ static int forward_expval_impl(const qsv_plan_t* p, const float* w, const float*
         if (!rc) rc = qsv_expval(p, d_state, B, out, wsc + mats_sz, readout_bytes(p, B), stream);
         return rc;
     }
-    double* part = (double*)(wsc + mats_sz);
+    // one tile per sample: its partials are the expectations (12 qubits and
+    // fewer with default tiles; a launch less)
+    const bool one = !p->multi && p->W <= p->opts.tile_qubits;
+    double* part = one ? out : (double*)(wsc + mats_sz);
     if ((rc = forward_impl(p, w, x, B, d_state, ws, s, T, part))) return rc;
+    if (one) return QSV_OK;
+    if (p->multi) return expval_final_multi(p, T, part, B, out, s);
     const int64_t ntiles = int64_t(1) << (p->W - std::min(p->opts.tile_qubits, p->W));
     hipEvent_t ev = prof_begin(p, s);
     hipLaunchKernelGGL(k_expval_final, dim3((unsigned)p->W, (unsigned)B), dim3(256), 0, s, (const double*)part,
@@ -2989,20 +3104,19 @@ int qsv_expval(const qsv_plan_t* p, const void* d_state, int64_t B, double* out,
         double* part = (double*)ws;
         const double amps = (double)B * (double)p->row;
         hipEvent_t ev = prof_begin(p, s);
-        hipLaunchKernelGGL(k_expval_part_multi, dim3((unsigned)p->nchunk_tot, (unsigned)B), dim3(256), 0, s,
-                           (const DCirc*)T->circ, (int)p->circ.size(), (const float2*)d_state, p->row,
-                           p->nchunk_tot, part);
+        if (fused_readout(p, T))
+            hipLaunchKernelGGL(k_expval_tiles_multi, dim3((unsigned)p->nchunk_tot, (unsigned)B), dim3(256), 0, s,
+                               (const DCirc*)T->circ, (int)p->circ.size(), (const DPass*)T->fwd_pass,
+                               (const float2*)d_state, p->row, p->nchunk_tot, part);
+        else
+            hipLaunchKernelGGL(k_expval_part_multi, dim3((unsigned)p->nchunk_tot, (unsigned)B), dim3(256), 0, s,
+                               (const DCirc*)T->circ, (int)p->circ.size(), (const float2*)d_state, p->row,
+                               p->nchunk_tot, part);
         prof_end(p, s, ev, K_EXPVAL_PART, 8.0 * amps, 3.0 * amps);
-        ev = prof_begin(p, s);
-        hipLaunchKernelGGL(k_expval_final_multi, dim3((unsigned)p->Wtot, (unsigned)B), dim3(256), 0, s,
-                           (const DCirc*)T->circ, (int)p->circ.size(), (const double*)part, p->nchunk_tot,
-                           p->Wtot, out);
-        prof_end(p, s, ev, K_EXPVAL_FINAL, 8.0 * (double)B * p->nchunk_tot * 32, 0.0);
-        HIP_TRY(hipGetLastError());
-        return QSV_OK;
+        return expval_final_multi(p, T, part, B, out, s);
     }
     const int64_t nchunk = expval_nchunk(p);
-    double* part = (double*)ws;
+    double* part = nchunk == 1 ? out : (double*)ws;  // one chunk per sample: nothing to sum
     const double amps = (double)B * (double)(int64_t(1) << p->W);
     hipEvent_t ev = prof_begin(p, s);
     const int vec = ((uintptr_t)d_state & 15) == 0;
@@ -3013,6 +3127,10 @@ int qsv_expval(const qsv_plan_t* p, const void* d_state, int64_t B, double* out,
         hipLaunchKernelGGL(k_expval_part<float2>, dim3((unsigned)nchunk, (unsigned)B), dim3(256), 0, s,
                            (const float2*)d_state, p->W, part, vec);
     prof_end(p, s, ev, K_EXPVAL_PART, (double)amp_size(p) * amps, 3.0 * amps);
+    if (nchunk == 1) {
+        HIP_TRY(hipGetLastError());
+        return QSV_OK;
+    }
     ev = prof_begin(p, s);
     hipLaunchKernelGGL(k_expval_final, dim3((unsigned)p->W, (unsigned)B), dim3(256), 0, s,
                        (const double*)part, p->W, nchunk, out);
@@ -3134,11 +3252,14 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
     const int n_out = p->n_weights + (gx ? (int)B * p->n_inputs : 0);
     if (n_out > 0) {
         hipEvent_t ev = prof_begin(p, s);
-        hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)n_out), dim3(256), 0, s,
-                           (const double*)part, T->grad_csr, p->n_weights, p->n_inputs, (int)B,
-                           (const int64_t*)T->pu, (const int32_t*)T->nchv, gw, gx, w,
-                           (int)p->opts.weight_remap,
-                           p->opts.method == QSV_METHOD_PER_GATE && !p->multi ? nch : int64_t(0));
+        const int64_t nch1 = p->opts.method == QSV_METHOD_PER_GATE && !p->multi ? nch : 0;
+        // partials of a weight: per gate it drives (one, mostly), B times its chunks
+        int64_t most = nch1;
+        for (int32_t v : p->nchv) most = nch1 ? most : std::max<int64_t>(most, v);
+        const bool few = B * most <= 512;
+        hipLaunchKernelGGL(few ? k_grad_reduce<64> : k_grad_reduce<256>, dim3((unsigned)(few ? (n_out + 3) / 4 : n_out)),
+                           dim3(256), 0, s, (const double*)part, T->grad_csr, p->n_weights, p->n_inputs, n_out, (int)B,
+                           (const int64_t*)T->pu, (const int32_t*)T->nchv, gw, gx, w, (int)p->opts.weight_remap, nch1);
         prof_end(p, s, ev, K_GRAD_REDUCE, 8.0 * (double)std::max<int64_t>(p->pu_total, 1) * B, 0.0);
     }
     HIP_TRY(hipGetLastError());
