@@ -572,7 +572,7 @@ __global__ __launch_bounds__(256) void k_expval_final(const double* __restrict__
 // Partial of ordinal o, sample b, chunk k at part[B * pu[o] + b * nch[o] + k];
 // with nch1 > 0 every ordinal has nch1 chunks instead. NT threads sum one
 // output: a block where outputs have many partials, a wave where they have few
-// (the 512-circuit set, 26,471 weights of at most 64 partials: 37 -> REDUCE_US us).
+// (the 512-circuit set, 26,471 weights of at most 64 partials: 37 -> 13 us).
 template <int NT>
 __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ part,
                                                      const int32_t* __restrict__ csr, int n_weights,
@@ -1518,7 +1518,7 @@ __device__ __forceinline__ int tile_base_of(const DPass* __restrict__ P, int tbi
 // <Z_i> partials of a tile whose final amplitudes are in the registers of the
 // load / store layout: out[i] = sum |a|^2 (1 - 2 bit_i) over the tile, float32
 // per thread (16 amplitudes), float64 above. Saves reading the state again (the
-// 512-circuit set, 195 MB: 65 -> READOUT_US us). lds: 52 doubles.
+// 512-circuit set, 195 MB: 65 us of readout become 30 us more in the passes). lds: 52 doubles.
 __device__ __forceinline__ void tile_readout(const DPass* __restrict__ P, const Lay& L, const float2 (&a)[kRegs],
                                              bool act, int W, int base, double* lds, double* __restrict__ out) {
     const int t = threadIdx.x, m = P->m, nv = 1 + m;  // total, 4 register bits, m - 4 thread bits
@@ -2300,8 +2300,14 @@ size_t state_bytes(const qsv_plan_t* p, int64_t B) { return (size_t)B * (size_t)
 constexpr size_t kLamSkew = 4096 + 256;
 
 size_t partial_bytes(const qsv_plan_t* p, int64_t B) {
-    const int64_t per = p->opts.method == QSV_METHOD_PER_GATE && !p->multi ? p->n_param * pg_nch(p, B) : p->pu_total;
-    return align256((size_t)std::max<int64_t>(per, 1) * B * sizeof(double));
+    int64_t n = p->pu_total * B;
+    if (p->opts.method == QSV_METHOD_PER_GATE && !p->multi) {
+        // at least B * pg_nch(B), and never less than a smaller batch needs
+        // (further split batches have at most 1,023 chunks)
+        const int64_t most = std::max(pg_chunks(p->W), int64_t(1) << std::max(p->W - 9, 0));
+        n = p->n_param * std::max(B * pg_chunks(p->W), std::min<int64_t>(B * most, 1024));
+    }
+    return align256((size_t)std::max<int64_t>(n, B) * sizeof(double));
 }
 
 
