@@ -479,13 +479,31 @@ class Plan:
         workspaces for calls that may run concurrently); calls on one stream
         reuse theirs in stream order."""
         import torch
-        n = qsv_workspace_size(self.handle, batch, op)
-        key = (op, str(device), torch.cuda.current_stream(device).cuda_stream)
-        ws = self._ws.get(key)
-        if ws is None or ws.numel() < n:
-            ws = torch.empty(max(n, 256), dtype=torch.uint8, device=device)
-            self._ws[key] = ws
-        return ws
+        device = torch.device(device)
+        index = torch.cuda.current_device() if device.index is None else device.index
+        return self._workspace(batch, op, index)[0]
+
+    def _workspace(self, batch, op, index):
+        """(workspace, its address, its bytes, stream handle, largest batch it was sized for) of
+        a call on GPU `index`. The library is asked for a size only when the batch is larger
+        than any before: sizes do not fall with the batch. The caller holds the tensor until
+        its kernels are queued, because another thread on this stream may replace the entry."""
+        if index is None:
+            raise ValueError("expected tensors on a GPU")
+        stream = _raw_stream(index)
+        key = (op, index, stream)
+        e = self._ws.get(key)
+        if e is None or e[4] < batch:
+            import torch
+            n = qsv_workspace_size(self.handle, batch, op)
+            if e is None or e[2] < n:
+                ws = torch.empty(max(n, 256), dtype=torch.uint8, device=torch.device("cuda", index))
+            else:
+                ws = e[0]
+            # a size of 0 reports an invalid batch, which the call itself rejects
+            e = (ws, ws.data_ptr(), ws.numel(), stream, batch if n else 0)
+            self._ws[key] = e
+        return e
 
     @staticmethod
     def _ptr(t):
@@ -502,9 +520,8 @@ class Plan:
         dev = weights.device if weights is not None and weights.numel() else inputs.device
         if state is None:
             state = torch.empty((batch, self.state_len), dtype=self.state_dtype(), device=dev)
-        ws = self.workspace(batch, OP_FORWARD, dev)
-        qsv_forward(self.handle, self._ptr(_f32(weights)), self._ptr(_f32(inputs)), batch,
-                    self._ptr(state), self._ptr(ws), ws.numel(), self._stream(dev))
+        held, ws, n, stream, _ = self._workspace(batch, OP_FORWARD, dev.index)
+        qsv_forward(self.handle, _f32_ptr(weights), _f32_ptr(inputs), batch, state.data_ptr(), ws, n, stream)
         return state
 
     def expval(self, state, out=None):
@@ -512,9 +529,8 @@ class Plan:
         batch = state.shape[0]
         if out is None:
             out = torch.empty((batch, self.n_out), dtype=torch.float64, device=state.device)
-        ws = self.workspace(batch, OP_EXPVAL, state.device)
-        qsv_expval(self.handle, self._ptr(state), batch, self._ptr(out), self._ptr(ws), ws.numel(),
-                   self._stream(state.device))
+        held, ws, n, stream, _ = self._workspace(batch, OP_EXPVAL, state.device.index)
+        qsv_expval(self.handle, state.data_ptr(), batch, out.data_ptr(), ws, n, stream)
         return out
 
     def forward_expval(self, weights, inputs, batch, state=None, out=None):
@@ -525,9 +541,9 @@ class Plan:
             state = torch.empty((batch, self.state_len), dtype=self.state_dtype(), device=dev)
         if out is None:
             out = torch.empty((batch, self.n_out), dtype=torch.float64, device=dev)
-        ws = self.workspace(batch, OP_FORWARD_EXPVAL, dev)
-        qsv_forward_expval(self.handle, self._ptr(_f32(weights)), self._ptr(_f32(inputs)), batch,
-                           self._ptr(state), self._ptr(out), self._ptr(ws), ws.numel(), self._stream(dev))
+        held, ws, n, stream, _ = self._workspace(batch, OP_FORWARD_EXPVAL, dev.index)
+        qsv_forward_expval(self.handle, _f32_ptr(weights), _f32_ptr(inputs), batch, state.data_ptr(), out.data_ptr(), ws,
+                           n, stream)
         return state, out
 
     def forward_expval_noalloc(self, weights, inputs, batch, state, out):
@@ -554,12 +570,23 @@ class Plan:
             gw = torch.empty((max(self.n_weights, 1),), dtype=torch.float64, device=dev)
         if gx is None and want_inputs and self.n_inputs:
             gx = torch.empty((batch, self.n_inputs), dtype=torch.float64, device=dev)
-        ws = self.workspace(batch, OP_BACKWARD, dev)
+        held, ws, n, stream, _ = self._workspace(batch, OP_BACKWARD, dev.index)
         go = grad_out.to(torch.float64).contiguous()
-        qsv_backward(self.handle, self._ptr(_f32(weights)), self._ptr(_f32(inputs)), batch,
-                     self._ptr(state), self._ptr(go), self._ptr(ws), ws.numel(), self._ptr(gw),
-                     self._ptr(gx) if want_inputs else None, self._stream(dev))
-        return gw[: self.n_weights], gx
+        qsv_backward(self.handle, _f32_ptr(weights), _f32_ptr(inputs), batch, state.data_ptr(), go.data_ptr(), ws, n,
+                     gw.data_ptr(), gx.data_ptr() if want_inputs and gx is not None else None, stream)
+        return (gw if gw.shape == (self.n_weights,) else gw[: self.n_weights]), gx
+
+
+def _raw_stream(index):
+    """Handle of torch's current stream on GPU `index`."""
+    import torch
+    return torch._C._cuda_getCurrentRawStream(index)
+
+
+def _f32_ptr(t):
+    """Address of a contiguous float32 tensor; None for no tensor or an empty one."""
+    t = _f32(t)
+    return None if t is None else t.data_ptr()
 
 
 def _f32(t):
