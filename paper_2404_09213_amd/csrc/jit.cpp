@@ -221,8 +221,8 @@ __device__ double qsv_chain_grad(const float* V, int axis, double cx, double cy,
     }
     return h00 * cz + hr * cx - hi * cy;
 }
-__device__ __forceinline__ unsigned qsv_sgn(int f, int k) { return ((unsigned)(f >> k) & 1u) << 31; }
-__device__ __forceinline__ f2 qsv_flip(f2 a, unsigned s) {
+__device__ __forceinline__ f2 qsv_flip(f2 a, unsigned w) {
+    const unsigned s = w & 0x80000000u;
     return make_float2(__uint_as_float(__float_as_uint(a.x) ^ s), __uint_as_float(__float_as_uint(a.y) ^ s));
 }
 )";
@@ -387,26 +387,75 @@ private:
 
     static std::string rk(const std::string& A, int k) { return A + "[" + I(k) + "]"; }
 
+    // Matrix-core operands of a pass. A matrix instruction can take its A operand
+    // from one block of four lanes for all 16 (cbsz 4, abid = the block), so one
+    // register holds the four columns of four gates: lane l has gate l >> 4, column
+    // (l >> 2) & 3, row l & 3 of the real 4x4 form of [[u00, u01], [u10, u11]] acting on
+    // (x.re, x.im, y.re, y.im). One load and one sign flip (row re, column im) per
+    // four consecutive matrix slots; the next group's load is issued when a group is
+    // first used. Selecting the columns from scalars took 16 vector instructions per
+    // gate, and a matrix instruction and a vector instruction of one SIMD do not
+    // overlap (20-qubit ladder, longest forward pass: 2,624 x 8 + 2,336 x 4 cycles a
+    // wave, 85% of the time it took). With this and the signs below, forward of the
+    // 20-qubit ladder, batch 64: 2.40 -> 2.07 ms; 12 qubits, batch 500: 43 -> 33 us.
+    struct AGroup { int mat; bool ps; };
+    std::vector<AGroup> agroups_;
+    std::vector<int> agroup_of_, ablock_of_;  // per op of the pass, from its first op
+    int aissued_ = 0, aop0_ = 0;
+    void plan_a_operands() {
+        agroups_.clear();
+        aissued_ = 0;
+        if (!ps_->n_stages) return;
+        aop0_ = p_->stages[ps_->stage0].op0;
+        const int n = p_->stages[ps_->stage0 + ps_->n_stages - 1].op1 - aop0_;
+        agroup_of_.assign(n, -1);
+        ablock_of_.assign(n, 0);
+        int open[2] = {-1, -1};  // open group of shared, per-sample matrices
+        for (int i = 0; i < n; ++i) {
+            const DOp& op = p_->ops[aop0_ + i];
+            if (!use_mfma(op)) continue;
+            const bool ps = op.mat < 0;
+            const int slot = ps ? -op.mat - 1 : op.mat;
+            int& g = open[ps];
+            if (g < 0 || slot < agroups_[g].mat || slot >= agroups_[g].mat + 4) {
+                g = (int)agroups_.size();
+                agroups_.push_back({slot, ps});
+            }
+            agroup_of_[i] = g;
+            ablock_of_[i] = 4 * (slot - agroups_[g].mat);
+        }
+        if (agroups_.empty()) return;
+        // byte offset of the lane's entry within its group and its sign; slots past
+        // the last matrix lie past the buffer's end and read as 0
+        o_ << "  const int ao_ = ((t & 0x30) << 1) | ((t & 2) << 3) | (t & 8) | (((t ^ (t >> 2)) & 1) << 2);\n"
+           << "  const unsigned as_ = (unsigned)((t >> 2) & ~t & 1) << 31;\n"
+           << "  const __amdgpu_buffer_rsrc_t mb_ = qsv_buf(mats, (unsigned)n_shared * 32u), "
+              "pb_ = qsv_buf(mp, (unsigned)n_ps * 32u); (void)mb_; (void)pb_;\n";
+        issue_a_group();
+    }
+    void issue_a_group() {
+        if (aissued_ >= (int)agroups_.size()) return;
+        const AGroup& g = agroups_[aissued_];
+        o_ << "  const unsigned am" << aissued_ << "_ = __builtin_amdgcn_raw_buffer_load_b32(" << (g.ps ? "pb_" : "mb_")
+           << ", ao_, " << 32 * g.mat << ", 0);\n";
+        ++aissued_;
+    }
+    // before an op: loads one group ahead of the first use of its own
+    void need_a_group(int op) {
+        const int g = agroups_.empty() ? -1 : agroup_of_[op - aop0_];
+        while (g >= 0 && aissued_ < std::min(g + 2, (int)agroups_.size())) issue_a_group();
+    }
+
     void emit_matrix(const DOp& op) {
         o_ << "    const float* M_ = " << mat_ptr(op.mat) << ";\n";
         switch (op.kind) {
         case OP_U2:
             if (use_mfma(op)) {
-                // row (lane & 3) of the real 4x4 form of [[u00, u01], [u10, u11]] acting
-                // on (x.re, x.im, y.re, y.im): rows 0, 1 from u00, u01; rows 2, 3 from u10, u11
-                // entries read as wave-uniform values (scalar loads), then selected per lane
-                o_ << "    float u_[8];\n"
-                   << "    for (int i_ = 0; i_ < 8; ++i_) u_[i_] = __int_as_float(__builtin_amdgcn_readfirstlane("
-                      "__float_as_int(M_[i_])));\n"
-                   << "    const float ur_ = lo4_ ? u_[0] : u_[4], ui_ = lo4_ ? u_[1] : u_[5], "
-                      "vr_ = lo4_ ? u_[2] : u_[6], vi_ = lo4_ ? u_[3] : u_[7];\n"
-                   << "    const float a0_ = im4_ ? ui_ : ur_, a1_ = im4_ ? ur_ : -ui_, "
-                      "a2_ = im4_ ? vi_ : vr_, a3_ = im4_ ? vr_ : -vi_;\n";
                 bool valu_too = false;
                 for (const std::string& A : arrays_) valu_too |= !mfma_array(A);
-                if (valu_too)
-                    o_ << "    const float m0r = u_[0], m0i = u_[1], m1r = u_[2], m1i = u_[3], "
-                          "m2r = u_[4], m2i = u_[5], m3r = u_[6], m3i = u_[7];\n";
+                if (!valu_too) break;
+                o_ << "    const float m0r = M_[0], m0i = M_[1], m1r = M_[2], m1i = M_[3], "
+                      "m2r = M_[4], m2i = M_[5], m3r = M_[6], m3i = M_[7];\n";
             } else {
                 o_ << "    const float m0r = M_[0], m0i = M_[1], m1r = M_[2], m1i = M_[3], "
                       "m2r = M_[4], m2i = M_[5], m3r = M_[6], m3i = M_[7];\n";
@@ -466,25 +515,38 @@ private:
     }
 
     // Matrix-core form of a generic 2x2 over every pair of every state array:
-    // 16 blocks of 4 lanes; lane 4b+j supplies row j of the gate's real 4x4
-    // form (A operand) and its own pair (B operand) and receives its pair's
-    // four outputs. The four rank-1 steps are issued step by step across all
+    // 16 blocks of 4 lanes; a lane supplies its own pair (B operand) and receives
+    // its pair's four outputs, the gate's real 4x4 form (A operand) comes from
+    // plan_a_operands(). The four rank-1 steps are issued step by step across all
     // pairs, so consecutive matrix instructions are independent.
     void emit_pairs_mfma(const DOp& op) {
-        std::vector<std::pair<std::string, std::string>> xy;
+        struct Pair { std::string first, second, a0, a1; };
+        std::vector<Pair> xy;
+        bool neg = false;
+        auto col = [&](int k) {
+            const bool n = neg_ >> k & 1;
+            neg |= n;
+            neg_ &= ~(1u << k);
+            return std::string(n ? "an_" : "am_");
+        };
         for (const std::string& A : arrays_)
             if (mfma_array(A))
-                for (int k : pairs(op)) xy.emplace_back(rk(A, k), rk(A, k | (1 << op.pos)));
+                for (int k : pairs(op)) {
+                    const int k1 = k | (1 << op.pos);
+                    xy.push_back({rk(A, k), rk(A, k1), col(k), col(k1)});
+                }
         const int n = (int)xy.size();
-        o_ << "    {\n";
+        const int at = (int)(&op - p_->ops.data()) - aop0_, ab = ablock_of_[at];
+        o_ << "    {\n      const float am_ = __uint_as_float(am" << agroup_of_[at] << "_ ^ as_);\n";
+        if (neg) o_ << "      const float an_ = __uint_as_float(am" << agroup_of_[at] << "_ ^ ~as_ & 0x80000000u);\n";
         for (int i = 0; i < n; ++i)
-            o_ << "      qsv_v4f c" << i << "_ = __builtin_amdgcn_mfma_f32_4x4x1f32(a0_, " << xy[i].first
-               << ".x, qsv_v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);\n";
+            o_ << "      qsv_v4f c" << i << "_ = __builtin_amdgcn_mfma_f32_4x4x1f32(" << xy[i].a0 << ", " << xy[i].first
+               << ".x, qsv_v4f{0.f, 0.f, 0.f, 0.f}, 4, " << ab << ", 0);\n";
         for (int st = 1; st < 4; ++st)
             for (int i = 0; i < n; ++i) {
                 const std::string src = st == 1 ? xy[i].first + ".y" : st == 2 ? xy[i].second + ".x" : xy[i].second + ".y";
-                o_ << "      c" << i << "_ = __builtin_amdgcn_mfma_f32_4x4x1f32(a" << st << "_, " << src << ", c" << i
-                   << "_, 0, 0, 0);\n";
+                o_ << "      c" << i << "_ = __builtin_amdgcn_mfma_f32_4x4x1f32(" << (st == 1 ? xy[i].a0 : xy[i].a1) << ", " << src << ", c" << i
+                   << "_, 4, " << ab + st << ", 0);\n";
             }
         for (int i = 0; i < n; ++i)
             o_ << "      " << xy[i].first << " = make_float2(c" << i << "_[0], c" << i << "_[1]); " << xy[i].second
@@ -558,7 +620,20 @@ private:
         }
     }
 
+    // Registers of a forward kernel that hold the negative of their amplitude:
+    // a matrix instruction takes the sign along (negated A operand), everything
+    // else has it applied first.
+    uint32_t neg_ = 0;
+    void apply_neg() {
+        for (int k = 0; k < kRegs; ++k)
+            if (neg_ >> k & 1)
+                for (const std::string& A : arrays_)
+                    o_ << "  " << rk(A, k) << " = make_float2(-" << rk(A, k) << ".x, -" << rk(A, k) << ".y);\n";
+        neg_ = 0;
+    }
+
     void emit_apply(const DOp& op) {
+        if (op.kind != OP_SIGN && !use_mfma(op)) apply_neg();
         o_ << "  {\n";
         if (op.kind == OP_SHY || op.kind == OP_SHX) {
             emit_shear(op);
@@ -572,26 +647,40 @@ private:
         }
         if (op.kind != OP_SIGN && op.kind != OP_SWAP) emit_matrix(op);
         if (op.kind == OP_SIGN) {
-            // uniform part folded at compile time, per-thread part from the index bits
-            const int nt = op.nterm;
-            if (nt) {
-                o_ << "    int f_ = 0;\n";
-                for (int i = 0; i < nt; ++i) {
-                    const DTerm& tm = p_->terms[op.term0 + i];
-                    std::string c = "(gT >> " + I(tm.s0) + ")";
-                    if (tm.s1 >= 0) c += " & (gT >> " + I(tm.s1) + ")";
-                    if (tm.s2 >= 0) c += " & (gT >> " + I(tm.s2) + ")";
-                    o_ << "    if ((" << c << ") & 1) f_ ^= " << hex(tm.mask) << ";\n";
-                }
+            // Uniform part folded at compile time. Per-thread part: one word per set
+            // of terms that some register is in, the term's sign in its top bit, so a
+            // flip is one instruction per component. (A word per register, from a mask
+            // of all terms, took three.)
+            std::vector<std::vector<int>> set_of(kRegs), sets;
+            for (int k = 0; k < kRegs; ++k) {
+                for (int i = 0; i < op.nterm; ++i)
+                    if (p_->terms[op.term0 + i].mask >> k & 1) set_of[k].push_back(i);
+                if (!set_of[k].empty() && std::find(sets.begin(), sets.end(), set_of[k]) == sets.end())
+                    sets.push_back(set_of[k]);
             }
+            for (int i = 0; i < op.nterm; ++i) {
+                const DTerm& tm = p_->terms[op.term0 + i];
+                o_ << "    const unsigned f" << i << "_ = ((unsigned)gT << " << 31 - tm.s0 << ")";
+                for (int s : {tm.s1, tm.s2})
+                    if (s >= 0) o_ << " & ((unsigned)gT << " << 31 - s << ")";
+                o_ << ";\n";
+            }
+            for (size_t j = 0; j < sets.size(); ++j) {
+                std::string w;
+                for (int i : sets[j]) w += (w.empty() ? "f" : " ^ f") + I(i) + "_";
+                o_ << "    const unsigned w" << j << "_ = " << w << ";\n";
+            }
+            const bool later = !bwd_ && (p_->opts.mfma & 1);  // matrix instructions take signs along
+            if (later) neg_ ^= (uint32_t)op.pos & 0xFFFF;
             for (const std::string& A : arrays_)
                 for (int k = 0; k < kRegs; ++k) {
-                    const bool u = op.pos >> k & 1;
-                    if (nt) {
-                        o_ << "    " << rk(A, k) << " = qsv_flip(" << rk(A, k) << ", qsv_sgn(f_"
-                           << (u ? " ^ 0xffff" : "") << ", " << k << "));\n";
+                    const bool u = !later && (op.pos >> k & 1);
+                    const std::string x = rk(A, k);
+                    if (!set_of[k].empty()) {
+                        const size_t j = std::find(sets.begin(), sets.end(), set_of[k]) - sets.begin();
+                        o_ << "    " << x << " = qsv_flip(" << x << ", " << (u ? "~w" : "w") << j << "_);\n";
                     } else if (u) {
-                        o_ << "    " << rk(A, k) << " = make_float2(-" << rk(A, k) << ".x, -" << rk(A, k) << ".y);\n";
+                        o_ << "    " << x << " = make_float2(-" << x << ".x, -" << x << ".y);\n";
                     }
                 }
             o_ << "  }\n";
@@ -856,7 +945,6 @@ private:
         // per-row float32 partials of every gradient slot: [wave * 4 + row][slot]
         if (bwd_ && ng) o_ << "  __shared__ float red[" << nw * 4 * ng << "];\n";
         o_ << "  const int t = threadIdx.x;\n";
-        o_ << "  const int q4_ = t & 3; const bool lo4_ = q4_ < 2, im4_ = q4_ & 1; (void)lo4_; (void)im4_;\n";
         if (guard_) o_ << "  const bool act = t < " << T_ << ";\n";
         // Workgroups are dealt to the chip's 8 XCDs in turn (workgroup i to XCD
         // i mod 8), each with its own L2. When the tile count divides by 8, XCD x
@@ -876,6 +964,7 @@ private:
         o_ << "  const size_t off = (size_t)b << " << W_ << ";\n"
            << "  const float* mp = mats + ((size_t)n_shared + (size_t)b * n_ps) * 8;\n"
            << "  (void)mp;\n";
+        plan_a_operands();
         const Layout nat = nat_layout();
         lds_own_ = false;
         // With tile bit 0 = amplitude bit 0 in registers 0 and 1 of each pair,
@@ -1001,6 +1090,7 @@ private:
             const DStage& st = p_->stages[ps_->stage0 + s];
             const Layout& L = lays[s];
             if (!same(L, cur)) {
+                apply_neg();
                 emit_exchange(cur, L);
                 cur = L;
             }
@@ -1008,12 +1098,16 @@ private:
             for (int oi = st.op0; oi < st.op1;) {
                 int oe = oi;
                 while (oe < st.op1 && is_grad_op(p_->ops[oe].kind)) ++oe;
-                if (oe == oi) emit_apply(p_->ops[oi++]);
+                if (oe == oi) {
+                    need_a_group(oi);
+                    emit_apply(p_->ops[oi++]);
+                }
                 else emit_grads(oi, oe);
                 oi = std::max(oi, oe);
             }
         }
         lay_ = nullptr;  // cur goes out of scope with this kernel
+        apply_neg();
         if (write_back) {
             if (!same(cur, nat)) {
                 emit_exchange(cur, nat);
