@@ -596,26 +596,30 @@ private:
                     const std::string x = rk(A, k), y = rk(A, k | (1 << op.pos));
                     const std::string to = step == 1 ? y : x, from = step == 1 ? x : y;
                     const char* c = step == 1 ? "b_" : "a_";
-                    // SHY: x -= a y, y += b x; SHX: x -= i a y, y -= i b x
-                    const char* sr = op.kind == OP_SHY && step != 1 ? "-" : "";
-                    const char* si = op.kind == OP_SHY && step == 1 ? "" : "-";
-                    const char* fr = op.kind == OP_SHY ? ".x" : ".y";
-                    const char* fi = op.kind == OP_SHY ? ".y" : ".x";
-                    o_ << "    " << to << ".x = fmaf(" << sr << c << ", " << from << fr << ", " << to << ".x); " << to
-                       << ".y = fmaf(" << si << c << ", " << from << fi << ", " << to << ".y);\n";
+                    const char* sg = step == 1 ? "" : "-";
+                    o_ << "    " << to << ".x = fmaf(" << sg << c << ", " << from << ".x, " << to << ".x); " << to
+                       << ".y = fmaf(" << sg << c << ", " << from << ".y, " << to << ".y);\n";
                 }
     }
 
-    // Waiting diagonals of the register qubits, one complex value per register index.
+    // Waiting diagonals of the register qubits, one complex value per register index;
+    // OP_DVEC2 adds the product with what rounding took off the value.
     void emit_dvec(const DOp& op) {
+        const bool res = op.kind == OP_DVEC2;
         o_ << "    const float* M_ = " << mat_ptr(op.mat) << ";\n";
         for (int k = 0; k < kRegs; ++k) {
             const int e = k & op.pos;
             if (!e) continue;
             o_ << "    { const float r_ = M_[" << 2 * e << "], i_ = M_[" << 2 * e + 1 << "];\n";
-            for (const std::string& A : arrays_)
-                o_ << "      { const f2 x = " << rk(A, k) << "; " << rk(A, k)
-                   << " = make_float2(r_ * x.x - i_ * x.y, r_ * x.y + i_ * x.x); }\n";
+            if (res) o_ << "      const float u_ = M_[" << 32 + 2 * e << "], v_ = M_[" << 33 + 2 * e << "];\n";
+            for (const std::string& A : arrays_) {
+                o_ << "      { const f2 x = " << rk(A, k) << "; " << rk(A, k) << " = ";
+                if (res)
+                    o_ << "make_float2(fmaf(r_, x.x, fmaf(-i_, x.y, fmaf(u_, x.x, -v_ * x.y))), "
+                          "fmaf(r_, x.y, fmaf(i_, x.x, fmaf(u_, x.y, v_ * x.x)))); }\n";
+                else
+                    o_ << "make_float2(r_ * x.x - i_ * x.y, r_ * x.y + i_ * x.x); }\n";
+            }
             o_ << "    }\n";
         }
     }
@@ -635,12 +639,12 @@ private:
     void emit_apply(const DOp& op) {
         if (op.kind != OP_SIGN && !use_mfma(op)) apply_neg();
         o_ << "  {\n";
-        if (op.kind == OP_SHY || op.kind == OP_SHX) {
+        if (op.kind == OP_SHEAR) {
             emit_shear(op);
             o_ << "  }\n";
             return;
         }
-        if (op.kind == OP_DVEC) {
+        if (op.kind == OP_DVEC || op.kind == OP_DVEC2) {
             emit_dvec(op);
             o_ << "  }\n";
             return;

@@ -35,33 +35,40 @@ enum RecipeKind : int32_t {
     RC_MATRIX = 0,  // 2x2: ordered product of `count` gates (recipe_gates[first ..]), optionally daggered
     RC_SHEAR = 1,   // shears of a rotation core (gates first .. first + count): [0] tan(phi/2), [1] sin(phi)
     RC_VMAT = 2,    // 2x2: P^dagger of the core (first2, count2) times the product of (first, count)
-    RC_DVEC = 3,    // 16 complex (4 slots): product of `count` factors (DFactor first ..) per register index
+    RC_DVEC = 3,    // 16 complex (4 slots): product of `count` factors (DFactor first ..) per register
+                    // index; core != 0: 4 more slots with what rounding took off each entry
 };
 struct DRecipe {
     int32_t kind, first, count, dagger, out;
     int32_t first2, count2;
-    int32_t core;   // CoreKind (RC_SHEAR, RC_VMAT)
+    int32_t core;   // CoreKind (RC_SHEAR, RC_VMAT); 1: with residuals (RC_DVEC)
     int32_t dir;    // 0 forward, 1 backward
 };
 
 // Rotation cores (backward of the generated kernels). A run of 1-qubit gates on
-// one qubit is lead diagonal gates, a core, and trailing diagonal gates. A core
-// is applied as
+// one qubit is lead diagonal gates, a core, and trailing diagonal gates. The
+// diagonals wait (they commute with everything but another core on the same
+// qubit) for one multiplication that covers all four register qubits. A core of
+// one rotation, or of fixed gates, is applied as its 2x2; any other as
 //   U = P R(phi) Q,  R = [[cos, -sin], [sin, cos]],  |phi| <= pi/2
-// with P, Q diagonal, up to a number. R is three shears, x -= a y, y += b x,
-// x -= a y with a = tan(phi/2), b = sin(phi): three multiply-adds per amplitude
-// component pair, in place, instead of the eight of a general 2x2. The phases
-// wait (they commute with everything but another core on the same qubit) for
-// one multiplication that covers all four register qubits. The forward keeps
-// the 2x2: rounding an SU(2) matrix leaves a multiple of an SU(2) matrix, which
-// moves expectations by less than rounding shears or phase vectors does (28-qubit
-// ring, E up to 3.6e-6 off instead of 4.2e-7); the gradients are not worse off.
+// with P, Q diagonal and waiting too, up to a number. R is three shears, x -= a y,
+// y += b x, x -= a y with a = tan(phi/2), b = sin(phi): three multiply-adds per
+// amplitude component pair, in place, instead of the eight of a general 2x2.
+// Precision decides where each form is used, against the gates' own 2x2 products,
+// whose rounding leaves a multiple of an SU(2) matrix and so moves expectations
+// and small gradients of large states least. The forward keeps these (28-qubit
+// ring, E up to 3.6e-6 off with shears and vectors instead of 4.2e-7). In the
+// backward a core of several rotations is no worse off as shears and a rounded
+// vector (22-qubit ladder, 5 inputs: gradients 2.4e-7 to 7.3e-7 off, 1.6e-7 to
+// 1.1e-6 with the products). One rotation can be (28-qubit ring, 7 inputs: 0.7 to
+// 1.6 times the products' error of 4e-7 to 7e-6), so it stays a 2x2, and vectors of
+// diagonal gates carry their entries' residuals (0.5 to 1.0 times; 16-qubit ring,
+// batch 256: 1.85 -> 1.91 ms per step, 28 qubits 47.1 -> 47.6 ms).
 enum CoreKind : int32_t {
     CORE_NONE = 0,
-    CORE_RY = 1,   // a single RY: R up to a sign, P = Q = 1
-    CORE_RX = 2,   // a single RX: R with -i sin on the off-diagonal up to a sign, P = Q = 1
-    CORE_GEN = 3,  // any other product holding an angle: P, phi, Q from its matrix
-    CORE_FIXED = 4 // no angle: applied as the plain 2x2
+    CORE_ROT = 1,  // a single RX or RY: its 2x2
+    CORE_GEN = 2,  // any other product holding an angle: P, phi, Q from its matrix
+    CORE_FIXED = 3 // no angle: its 2x2
 };
 
 // One diagonal factor (f0, f1) of a RC_DVEC recipe, entering as (1, f1 / f0) on
@@ -87,10 +94,10 @@ enum OpKind : int32_t {
     OP_GY = 7,     // gradient partial, generator Y on `pos`
     OP_GZ = 8,     // gradient partial, generator Z; pos >= 0 register, else `sh`
     // generated backward kernels only, on register position `pos` (a, b: the slot's values):
-    OP_SHY = 9,    // R of a core: x -= a y, y += b x, x -= a y
-    OP_SHX = 10,   // R of a RX core: the same with i y for y
+    OP_SHEAR = 9,  // R of a core: x -= a y, y += b x, x -= a y
     OP_DVEC = 11,  // multiply register k by complex entry k & pos of 4 slots from `mat`, where it
                    // is not 1 (k has a bit of the mask `pos`)
+    OP_DVEC2 = 12, // the same with the entries' residuals in 4 more slots
 };
 // table-driven backward: components only, nothing is applied
 constexpr int32_t OP_NONE = 13;

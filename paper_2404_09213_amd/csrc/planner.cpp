@@ -162,14 +162,14 @@ int add_recipe(qsv_plan_t* p, const std::vector<int>& gs, bool dagger) {
 }
 
 // Shear of a rotation core (RC_SHEAR).
-int add_shear(qsv_plan_t* p, const std::vector<int>& gs, int core, bool dagger) {
+int add_shear(qsv_plan_t* p, const std::vector<int>& gs, bool dagger) {
     DRecipe r;
     std::memset(&r, 0, sizeof r);
     r.kind = RC_SHEAR;
     r.first = put_gates(p, gs);
     r.count = (int32_t)gs.size();
     r.dagger = dagger ? 1 : 0;
-    r.core = core;
+    r.core = CORE_GEN;
     return put_recipe(p, r, any_input(p, gs), 1);
 }
 
@@ -194,10 +194,11 @@ struct Factor {
 };
 
 // Product of factors (RC_DVEC).
-int add_factors(qsv_plan_t* p, const std::vector<Factor>& fs) {
+int add_factors(qsv_plan_t* p, const std::vector<Factor>& fs, bool residuals) {
     DRecipe r;
     std::memset(&r, 0, sizeof r);
     r.kind = RC_DVEC;
+    r.core = residuals ? 1 : 0;
     bool per_sample = false;
     std::vector<DFactor> d;
     for (const Factor& f : fs) {
@@ -214,7 +215,7 @@ int add_factors(qsv_plan_t* p, const std::vector<Factor>& fs) {
     r.first = (int32_t)p->factors.size();
     r.count = (int32_t)d.size();
     p->factors.insert(p->factors.end(), d.begin(), d.end());
-    return put_recipe(p, r, per_sample, 4);
+    return put_recipe(p, r, per_sample, residuals ? 8 : 4);
 }
 
 std::vector<Block> split(const qsv_plan_t* p, const std::vector<int>& seq, int k) {
@@ -667,10 +668,7 @@ void classify_core(const qsv_plan_t* p, Unit& u) {
     bool param = false;
     for (int j = a; j < b; ++j) param |= p->gates[u.gates[j]].src != QSV_SRC_NONE;
     const int k = p->gates[u.gates[a]].kind;
-    u.core = !param ? CORE_FIXED
-             : b - a == 1 && k == QSV_RY ? CORE_RY
-             : b - a == 1 && k == QSV_RX ? CORE_RX
-                                         : CORE_GEN;
+    u.core = !param ? CORE_FIXED : b - a == 1 && (k == QSV_RY || k == QSV_RX) ? CORE_ROT : CORE_GEN;
 }
 
 // Pauli components a chain's gradients need, taken between its core and its
@@ -694,8 +692,8 @@ int core_comps(const qsv_plan_t* p, const Unit& u, int& nparam) {
 // Backward units of the generated kernels, in uncompute order. A run of
 // 1-qubit gates is [lead diagonals] and [core, trailing diagonals]; the latter
 // is one unit when that takes fewer vector operations per amplitude than gate
-// by gate (a shear costs 2 per state, a component 2, a pending diagonal 1 per
-// state when four qubits share its multiplication) and needs no more
+// by gate (a rotation costs 4 per state as its 2x2 and 3 as shears, a component 2,
+// a pending diagonal 1 per state when four qubits share its multiplication) and needs no more
 // components than it has angles.
 std::vector<Unit> bwd_core_units(const qsv_plan_t* p, const std::vector<int>& gates, bool fuse) {
     std::vector<Unit> out;
@@ -1057,7 +1055,12 @@ struct PassBuilder {
                 if (!f.empty()) {
                     DOp o;
                     std::memset(&o, 0, sizeof o);
+                    // factors of general cores only: no residuals (see CoreKind)
                     o.kind = OP_DVEC;
+                    for (const Factor& x : f)
+                        if (x.kind == F_DIAG) o.kind = OP_DVEC2;
+                    for (const Factor& x : f)
+                        if (x.kind != F_DIAG) o.kind = OP_DVEC;
                     o.pos = mask;
                     o.ctl = o.ctl2 = -1;
                     o.slot = -1;
@@ -1165,12 +1168,12 @@ struct PassBuilder {
                     o.sh = W - 1 - U.qubit;
                     o.ctl = o.ctl2 = -1;
                     o.slot = -1;
-                    if (U.core == CORE_FIXED) {
+                    if (U.core == CORE_GEN) {
+                        o.kind = OP_SHEAR;
+                        o.mat = add_shear(p, core, true);
+                    } else {
                         o.kind = recipe_class(p, core);
                         o.mat = add_recipe(p, core, true);
-                    } else {
-                        o.kind = U.core == CORE_RX ? OP_SHX : OP_SHY;
-                        o.mat = add_shear(p, core, U.core, true);
                     }
                     sign_op = -1;
                     p->ops.push_back(o);
@@ -1268,7 +1271,7 @@ struct PassBuilder {
             st.op1 = (int32_t)p->ops.size();
             p->stages.push_back(st);
         }
-        for (auto& v : wait.vecs) p->ops[v.op].mat = add_factors(p, v.f);
+        for (auto& v : wait.vecs) p->ops[v.op].mat = add_factors(p, v.f, p->ops[v.op].kind == OP_DVEC2);
         lay_out(ps, m);
         ps.n_gslots = nslot;
         ps.n_gout = (int32_t)p->gouts.size() - ps.gout0;
@@ -1286,8 +1289,9 @@ double op_flops(const DOp& o) {
     case OP_DIAG: return 6.0 * half;
     case OP_GX: case OP_GY: return 3.5 * half;
     case OP_GZ: return 4.0 * half;
-    case OP_SHY: case OP_SHX: return 6.0;  // three multiply-adds per amplitude
+    case OP_SHEAR: return 6.0;  // three multiply-adds per amplitude
     case OP_DVEC: return 6.0 * (1.0 - 1.0 / (double)(1 << popc((uint32_t)o.pos)));
+    case OP_DVEC2: return 14.0 * (1.0 - 1.0 / (double)(1 << popc((uint32_t)o.pos)));
     default: return 0.0;               // sign flips and swaps move data only
     }
 }

@@ -307,9 +307,9 @@ __device__ __forceinline__ CoreParts coef_core(const double (&M)[8], int core) {
     CoreParts o;
     o.p0 = o.p1 = o.q1 = make_double2(1.0, 0.0);
     double c, s;
-    if (core != CORE_GEN) {
-        c = M[0];
-        s = core == CORE_RX ? -M[5] : M[4];
+    if (core != CORE_GEN) {  // no core: nothing of it is used
+        c = 1.0;
+        s = 0.0;
     } else {
         const double2 a = make_double2(M[0], M[1]), d = make_double2(M[4], M[5]);
         c = sqrt(a.x * a.x + a.y * a.y);
@@ -450,6 +450,10 @@ __global__ __launch_bounds__(64) void k_coef(CoefIn in, const DRecipe* __restric
     if (vec && lane < 16) {
         dst[2 * lane] = (R)D.x;
         dst[2 * lane + 1] = (R)D.y;
+        if (Rc.core) {  // what rounding took off
+            dst[32 + 2 * lane] = (R)(D.x - (double)(R)D.x);
+            dst[33 + 2 * lane] = (R)(D.y - (double)(R)D.y);
+        }
     }
 }
 
