@@ -127,16 +127,19 @@ __device__ __forceinline__ f2 qsv_ld2(__amdgpu_buffer_rsrc_t b, int off, int c) 
     const qsv_u2 v = __builtin_amdgcn_raw_buffer_load_b64(b, off, c, 0);
     return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
 }
+// NT: non-temporal
+template <int NT>
 __device__ __forceinline__ float4 qsv_ld4(__amdgpu_buffer_rsrc_t b, int off, int c) {
-    const qsv_u4 v = __builtin_amdgcn_raw_buffer_load_b128(b, off, c, 0);
+    const qsv_u4 v = __builtin_amdgcn_raw_buffer_load_b128(b, off, c, NT ? 2 : 0);
     return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
 __device__ __forceinline__ void qsv_st2(f2 a, __amdgpu_buffer_rsrc_t b, int off, int c) {
     __builtin_amdgcn_raw_buffer_store_b64(qsv_u2{__float_as_uint(a.x), __float_as_uint(a.y)}, b, off, c, 0);
 }
+template <int NT>
 __device__ __forceinline__ void qsv_st4(float4 a, __amdgpu_buffer_rsrc_t b, int off, int c) {
     __builtin_amdgcn_raw_buffer_store_b128(
-        qsv_u4{__float_as_uint(a.x), __float_as_uint(a.y), __float_as_uint(a.z), __float_as_uint(a.w)}, b, off, c, 0);
+        qsv_u4{__float_as_uint(a.x), __float_as_uint(a.y), __float_as_uint(a.z), __float_as_uint(a.w)}, b, off, c, NT ? 2 : 0);
 }
 // float64 wavefront sum by DPP lane moves: pairs, quads, half rows, rows, then
 // row 0 -> 1, 2 -> 3 and rows 0-1 -> 2-3 broadcasts; lane 63 holds the total.
@@ -990,8 +993,22 @@ private:
         auto open = [&](const std::string& name, const std::string& ptr) {
             return buf ? "const __amdgpu_buffer_rsrc_t " + name + "b_ = qsv_buf(" + ptr + ", " + I(8LL << W_) + "u); " : std::string();
         };
+        // Non-temporal where the arrays a launch passes over exceed the 256 MB Infinity
+        // Cache twice: nothing of them is left when the next pass comes (28-qubit ring,
+        // 2.1 GB a state: 47.4 -> 45.4 ms per step; 4-layer rings' backward, 0.5 GB of psi
+        // and lambda: 2.36 -> 2.31 ms, 1.1 GB: 4.24 -> 4.07). Below, passes find part of
+        // them there (16-qubit ring, batch 256, 0.13 GB a state: 1.93 -> 2.08 ms with
+        // them; 21 qubits, batch 7, forward: 760 -> 857 us).
+        const bool nt = buf && v16;
+        if (nt)
+            o_ << "  const bool nt_ = gridDim.x >= " << ((512u << 20) / ((8u << m_) * (unsigned)arrays_.size())) << "u;\n";
+        // by alignment (8 bytes: s1, 16: s2) and size (s3)
+        auto by_access = [&](const std::string& ptr, const std::string& s1, const std::string& s2, const std::string& s3) {
+            const std::string two = "if (((qsv_uptr)(" + ptr + ") & 15) != 0) { " + s1 + "} else ";
+            return two + (nt ? "if (nt_) { " + s3 + "} else { " + s2 + "}" : "{ " + s2 + "}");
+        };
         auto gload = [&](const std::string& A, const std::string& src) {
-            std::string s1, s2;
+            std::string s1, s2, s3;
             for (int k = 0; k < kRegs; ++k) {
                 s1 += A + "[" + I(k) + "] = ";
                 if (buf) s1 += "qsv_ld2(" + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + "); ";
@@ -999,15 +1016,19 @@ private:
             }
             if (!v16) return "{ " + open(A, src) + s1 + "}";
             for (int k = 0; k < kRegs; k += 2) {
-                s2 += "{ const float4 v_ = ";
-                if (buf) s2 += "qsv_ld4(" + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + ")";
-                else s2 += "*reinterpret_cast<const float4*>(" + src + " + gT + " + I(gR(cur, k)) + ")";
-                s2 += "; " + A + "[" + I(k) + "] = make_float2(v_.x, v_.y); " + A + "[" + I(k + 1) + "] = make_float2(v_.z, v_.w); } ";
+                auto pair = [&](const std::string& load) {
+                    return "{ const float4 v_ = " + load + "; " + A + "[" + I(k) + "] = make_float2(v_.x, v_.y); " + A + "[" +
+                           I(k + 1) + "] = make_float2(v_.z, v_.w); } ";
+                };
+                const std::string at = "(" + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + ")";
+                s2 += pair(buf ? "qsv_ld4<0>" + at
+                               : "*reinterpret_cast<const float4*>(" + src + " + gT + " + I(gR(cur, k)) + ")");
+                if (nt) s3 += pair("qsv_ld4<1>" + at);
             }
-            return "{ " + open(A, src) + "if (((qsv_uptr)(" + src + ") & 15) == 0) { " + s2 + "} else { " + s1 + "} }";
+            return "{ " + open(A, src) + by_access(src, s1, s2, s3) + " }";
         };
         auto gstore = [&](const std::string& A, const std::string& dst) {
-            std::string s1, s2;
+            std::string s1, s2, s3;
             for (int k = 0; k < kRegs; ++k) {
                 const std::string v = A + "[" + I(k) + "]";
                 if (buf) s1 += "qsv_st2(" + v + ", " + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + "); ";
@@ -1017,10 +1038,12 @@ private:
             for (int k = 0; k < kRegs; k += 2) {
                 const std::string x = A + "[" + I(k) + "]", y = A + "[" + I(k + 1) + "]";
                 const std::string v = "make_float4(" + x + ".x, " + x + ".y, " + y + ".x, " + y + ".y)";
-                if (buf) s2 += "qsv_st4(" + v + ", " + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + "); ";
+                const std::string at = "(" + v + ", " + A + "b_, gT << 3, " + I(gR(cur, k) * 8) + "); ";
+                if (buf) s2 += "qsv_st4<0>" + at;
                 else s2 += "*reinterpret_cast<float4*>(" + dst + " + gT + " + I(gR(cur, k)) + ") = " + v + "; ";
+                if (nt) s3 += "qsv_st4<1>" + at;
             }
-            return "{ " + open(A, dst) + "if (((qsv_uptr)(" + dst + ") & 15) == 0) { " + s2 + "} else { " + s1 + "} }";
+            return "{ " + open(A, dst) + by_access(dst, s1, s2, s3) + " }";
         };
         const int flags = ps_->flags;
         if (!bwd_ && (flags & PF_INIT_FWD)) {
