@@ -344,10 +344,10 @@ int qsv_forward_expval(const qsv_plan_t* plan, const float* d_weights, const flo
  *    qsv_forward, qsv_forward_expval, qsv_expval, qsv_backward or
  *    qsv_graph_create call on this device creates them (for a multi-circuit
  *    plan, at this batch size). Otherwise QSV_ERR_ARG, nothing enqueued.
- *  - A plan and batch whose forward gate matrices and readout partials (part
- *    of qsv_workspace_size(plan, batch, QSV_OP_FORWARD_EXPVAL), which also
- *    leaves room for the backward's matrices) exceed QSV_NOALLOC_SCRATCH_BYTES
- *    return QSV_ERR_TOO_BIG before anything is enqueued.
+ *  - A plan and batch whose forward gate matrices and readout partials exceed
+ *    QSV_NOALLOC_SCRATCH_BYTES return QSV_ERR_TOO_BIG before anything is
+ *    enqueued. (qsv_workspace_size(plan, batch, QSV_OP_FORWARD_EXPVAL) may be
+ *    more: its matrix part serves both directions.)
  *  - Every call on one GPU shares that GPU's array, which keeps the last
  *    call's contents (each call writes everything it reads, so nothing needs
  *    clearing). Calls that may overlap on one GPU (other streams, threads or

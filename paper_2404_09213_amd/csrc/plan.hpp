@@ -270,10 +270,6 @@ struct qsv_plan_s {
     // matrix slots of the forward [0] and of the backward [1], shared and per
     // sample; each call evaluates its own direction's recipes
     int n_shared_mats[2] = {0, 0}, n_ps_mats[2] = {0, 0};
-    // slots of both directions with one 2x2 per applied gate run and per
-    // gradient conjugation, as the table-driven kernels have them: workspaces
-    // never get smaller than that
-    int ref_shared = 0, ref_ps = 0;
     // recipes per direction: shared, shared vectors, per-sample, per-sample vectors (stored in this order)
     int n_recipe_cls[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
     int dir = 0;           // direction whose recipes are being added

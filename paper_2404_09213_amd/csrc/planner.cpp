@@ -842,23 +842,6 @@ struct Waiting {
     explicit Waiting(int W) : diag(W) {}
 };
 
-// Adds the matrix slots that the table-driven kernels have for one pass of a
-// generated plan to p->ref_shared / ref_ps.
-void count_ref_slots(qsv_plan_t* p, const std::vector<Unit>& units, const std::vector<int>& first_on) {
-    auto add = [&](const std::vector<int>& gs) { ++(any_input(p, gs) ? p->ref_ps : p->ref_shared); };
-    for (const Unit& U : units) {
-        const int n = (int)U.gates.size();
-        if (n == 1 && is_zz(p->gates[U.gates[0]].kind)) continue;
-        for (int j = 0; U.comps && j + 1 < n; ++j)
-            if (p->gates[U.gates[j]].src != QSV_SRC_NONE)
-                add(std::vector<int>(U.gates.begin() + j + 1, U.gates.end()));
-        bool starts = !first_on.empty();
-        for (int b = 0; b < p->W && starts; ++b)
-            if ((qmask(p->gates[U.gates[0]]) >> b & 1) && first_on[b] != U.gates[0]) starts = false;
-        if (!starts) add(U.gates);
-    }
-}
-
 // Builds one DPass (tile qubits + stages + ops) from a pass's gate list.
 struct PassBuilder {
     qsv_plan_t* p;
@@ -924,7 +907,6 @@ struct PassBuilder {
         const bool cores = backward && p->opts.codegen != 0;  // rotation cores
         std::vector<Unit> units = cores ? bwd_core_units(p, gates, fuse) : backward ? bwd_units(p, gates, fuse)
                                                                                      : fwd_units(p, gates);
-        count_ref_slots(p, cores ? bwd_units(p, gates, fuse) : units, first_on);
         auto groups = group_stages(units);
         // register qubits of every stage: its dense qubits, padded with the top local bits
         std::vector<std::vector<int>> stage_regs;
@@ -1372,10 +1354,6 @@ int build_plan(qsv_plan_t* p) {
     const int rc = build_schedule(p);
     if (rc != QSV_OK) return rc;
     sort_recipes(p);
-    if (p->opts.method == QSV_METHOD_PER_GATE) {
-        p->ref_shared = p->n_shared_mats[0] + p->n_shared_mats[1];
-        p->ref_ps = p->n_ps_mats[0] + p->n_ps_mats[1];
-    }
     return QSV_OK;
 }
 
@@ -1430,10 +1408,7 @@ int build_schedule(qsv_plan_t* p) {
         }
     }
     p->prefix_mat.resize(W);
-    for (int q = 0; q < W; ++q) {
-        p->prefix_mat[q] = add_recipe(p, pre[q], false);
-        ++(p->prefix_mat[q] < 0 ? p->ref_ps : p->ref_shared);
-    }
+    for (int q = 0; q < W; ++q) p->prefix_mat[q] = add_recipe(p, pre[q], false);
     std::vector<int> body, all;
     for (int g = 0; g < p->n_gates; ++g) {
         all.push_back(g);
@@ -1603,8 +1578,6 @@ int build_multi(qsv_plan_t* p, const std::vector<CircuitIn>& cs) {
             p->n_shared_mats[d2] += sub.n_shared_mats[d2];
             p->n_ps_mats[d2] += sub.n_ps_mats[d2];
         }
-        p->ref_shared += sub.ref_shared;
-        p->ref_ps += sub.ref_ps;
         for (int32_t m : sub.prefix_mat) p->prefix_mat.push_back(fix_mat(m, 0));
         for (DStage st : sub.stages) {
             st.op0 += op0;

@@ -2295,18 +2295,13 @@ int get_tables(const qsv_plan_t* p, DeviceTables** out) {
 bool c128(const qsv_plan_t* p) { return p->opts.amp_dtype == QSV_AMP_C128; }
 size_t amp_size(const qsv_plan_t* p) { return c128(p) ? 16 : 8; }
 
-size_t mats_bytes(const qsv_plan_t* p, int64_t B) {
-    const int sh = std::max(std::max(p->n_shared_mats[0], p->n_shared_mats[1]), p->ref_shared);
-    const int ps = std::max(std::max(p->n_ps_mats[0], p->n_ps_mats[1]), p->ref_ps);
-    return align256(((size_t)sh + (size_t)B * ps) * 8 * (amp_size(p) / 2) + 32);
+// Gate matrices of one direction (0 forward, 1 backward), as run_coef lays them out.
+size_t dir_mats_bytes(const qsv_plan_t* p, int64_t B, int dir) {
+    return align256(((size_t)p->n_shared_mats[dir] + (size_t)B * p->n_ps_mats[dir]) * 8 * (amp_size(p) / 2) + 32);
 }
 
-// The matrices of a forward alone, as the allocation-free call lays them out
-// (and counts them against its limit): ref_shared and ref_ps are never less
-// than the forward's own slots.
-size_t fwd_mats_bytes(const qsv_plan_t* p, int64_t B) {
-    return align256(((size_t)p->ref_shared + (size_t)B * p->ref_ps) * 8 * (amp_size(p) / 2) + 32);
-}
+// Matrix part of every workspace: either direction's.
+size_t mats_bytes(const qsv_plan_t* p, int64_t B) { return std::max(dir_mats_bytes(p, B, 0), dir_mats_bytes(p, B, 1)); }
 
 // Chunks per sample of the plain method's backward launches and partials: as
 // planned (4096 amplitudes each) where these fill the chip, else up to eight
@@ -3109,7 +3104,7 @@ int qsv_forward_expval_noalloc(const qsv_plan_t* p, const float* w, const float*
         set_error("null pointer");
         return QSV_ERR_ARG;
     }
-    const size_t need = fwd_mats_bytes(p, B) + readout_bytes(p, B);
+    const size_t need = dir_mats_bytes(p, B, 0) + readout_bytes(p, B);
     if (need > (size_t)QSV_NOALLOC_SCRATCH_BYTES) {
         char buf[160];
         std::snprintf(buf, sizeof buf, "this plan and batch need %zu bytes of scratch, above the %zu-byte "
@@ -3122,7 +3117,7 @@ int qsv_forward_expval_noalloc(const qsv_plan_t* p, const float* w, const float*
     // the same launches as qsv_forward_expval on the scratch array; g_noalloc
     // turns every lazy creation (tables, kernels, work lists, events) into an error
     g_noalloc = true;
-    rc = forward_expval_impl(p, w, x, B, d_state, out, ws, fwd_mats_bytes(p, B), stream);
+    rc = forward_expval_impl(p, w, x, B, d_state, out, ws, dir_mats_bytes(p, B, 0), stream);
     g_noalloc = false;
     return rc;
 }
