@@ -480,6 +480,8 @@ class Plan:
         reuse theirs in stream order."""
         import torch
         device = torch.device(device)
+        if device.type != "cuda":
+            raise ValueError(f"expected a GPU, not {device}")
         index = torch.cuda.current_device() if device.index is None else device.index
         return self._workspace(batch, op, index)[0]
 
