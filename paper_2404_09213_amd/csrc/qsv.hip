@@ -591,66 +591,73 @@ __global__ __launch_bounds__(256) void k_expval_final(const double* __restrict__
 // gradient reduction: partials[(ordinal * B + b) * nch + chunk]
 // ----------------------------------------------------------------------------
 // Partial of ordinal o, sample b, chunk k at part[B * pu[o] + b * nch[o] + k];
-// with nch1 > 0 every ordinal has nch1 chunks instead. NT threads sum one
-// output: a block where outputs have many partials, a wave where they have few
-// (the 512-circuit set, 26,471 weights of at most 64 partials: 37 -> 13 us).
+// with nch1 > 0 every ordinal has nch1 chunks instead.
+//
+// Thread t's part (of NT) of the partials of the ordinals in `list`, samples b0 to b0 + nb
 template <int NT>
+__device__ __forceinline__ double partial_sum(const double* __restrict__ part, const int32_t* __restrict__ list, int nl,
+                                              int b0, int nb, int B, const int64_t* __restrict__ pu,
+                                              const int32_t* __restrict__ nchv, int64_t nch1, int t) {
+    double s = 0.0;
+    for (int l = 0; l < nl; ++l) {
+        const int q = list[l];
+        const int64_t nch = nch1 > 0 ? nch1 : nchv[q];
+        const double* base = part + (int64_t)B * (nch1 > 0 ? q * nch1 : pu[q]) + (int64_t)b0 * nch;
+        s += strided_sum<NT>(base, (int64_t)nb * nch, 1, t);
+    }
+    return s;
+}
+
+// Sum over the NT threads of one output (256: the block, 64: a wave)
+template <int NT>
+__device__ __forceinline__ double group_sum(double s, double* red) {
+    if (NT == 1) return s;
+    s = wave_sum(s);
+    if (NT == 256) {
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+        __syncthreads();
+        s = red[0] + red[1] + red[2] + red[3];
+    }
+    return s;
+}
+
+// The first n_wblocks blocks sum weight gradients, NW threads per weight, the others input
+// gradients, NI threads per input and sample. A weight has a partial per sample and
+// chunk, an input's gradient only its sample's: as many threads as weights need
+// leave all but a few idle there, and a launch of many samples is then bound by its
+// blocks (8 qubits, batch 8,192, ten partials an input: 276 us with a block each, 13 with a
+// thread each). A wave per weight where those have few partials, too: 512 circuits, 26,471
+// weights of at most 64 partials, 37 -> 13 us.
+template <int NW, int NI>
 __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ part,
                                                      const int32_t* __restrict__ csr, int n_weights,
-                                                     int n_inputs, int n_out, int B,
+                                                     int n_inputs, int n_wblocks, int B,
                                                      const int64_t* __restrict__ pu,
                                                      const int32_t* __restrict__ nchv,
                                                      double* __restrict__ gw,
                                                      double* __restrict__ gx,
                                                      const float* __restrict__ weights, int remap, int64_t nch1) {
     __shared__ double red[4];
-    const int t = threadIdx.x % NT;
-    const int o = blockIdx.x * (256 / NT) + threadIdx.x / NT;  // output index: weights first, then (b, input)
-    if (o >= n_out) return;  // whole waves, and only in the last block of the wave variant
-    double s = 0.0;
-    int j, b0, b1;
-    const int32_t* list;
-    int nl;
-    if (o < n_weights) {
-        j = o;
-        list = csr + csr[j];
-        nl = csr[j + 1] - csr[j];
-        b0 = 0;
-        b1 = B;
-    } else {
-        const int r = o - n_weights;
-        const int b = r / n_inputs;
-        j = r % n_inputs;
-        const int32_t* xo = csr + n_weights + 1;
-        list = csr + xo[j];
-        nl = xo[j + 1] - xo[j];
-        b0 = b;
-        b1 = b + 1;
-    }
-    for (int l = 0; l < nl; ++l) {
-        const int q = list[l];
-        const int64_t nch = nch1 > 0 ? nch1 : nchv[q];
-        const int64_t per = (int64_t)(b1 - b0) * nch;
-        const double* base = part + (int64_t)B * (nch1 > 0 ? q * nch1 : pu[q]) + (int64_t)b0 * nch;
-        s += strided_sum<NT>(base, per, 1, t);
-    }
-    s = wave_sum(s);
-    if (NT == 256) {
-        if ((t & 63) == 0) red[t >> 6] = s;
-        __syncthreads();
-        s = red[0] + red[1] + red[2] + red[3];
-    }
-    if (t == 0) {
-        if (o < n_weights) {
-            double f = 1.0;
-            if (remap) {  // d(pi tanh w)/dw
-                const double th = tanh((double)weights[j]);
-                f = M_PI * (1.0 - th * th);
-            }
-            gw[j] = s * f;
+    if ((int)blockIdx.x < n_wblocks) {
+        const int j = blockIdx.x * (256 / NW) + threadIdx.x / NW, t = threadIdx.x % NW;
+        if (j >= n_weights) return;  // whole waves, and only where a wave has an output
+        const double s = group_sum<NW>(partial_sum<NW>(part, csr + csr[j], csr[j + 1] - csr[j], 0, B, B, pu, nchv, nch1, t), red);
+        if (t) return;
+        double f = 1.0;
+        if (remap) {  // d(pi tanh w)/dw
+            const double th = tanh((double)weights[j]);
+            f = M_PI * (1.0 - th * th);
         }
-        else if (gx) gx[(size_t)b0 * n_inputs + j] = s;
+        gw[j] = s * f;
+        return;
     }
+    const int i = (blockIdx.x - n_wblocks) * (256 / NI) + threadIdx.x / NI, t = threadIdx.x % NI;
+    if (i >= B * n_inputs) return;  // whole waves where a wave has an output
+    // a thread per output: neighbours take neighbouring samples, whose partials are neighbours
+    const int b = NI == 1 ? i % B : i / n_inputs, j = NI == 1 ? i / B : i % n_inputs;
+    const int32_t* xo = csr + n_weights + 1;
+    const double s = group_sum<NI>(partial_sum<NI>(part, csr + xo[j], xo[j + 1] - xo[j], b, 1, B, pu, nchv, nch1, t), red);
+    if (t == 0) gx[(size_t)b * n_inputs + j] = s;
 }
 
 // ----------------------------------------------------------------------------
@@ -3283,17 +3290,21 @@ int qsv_backward(const qsv_plan_t* p, const float* w, const float* x, int64_t B,
                      T->bwd_fn.empty() ? -1 : (int)i);
         }
     }
-    const int n_out = p->n_weights + (gx ? (int)B * p->n_inputs : 0);
-    if (n_out > 0) {
+    const int n_gx = gx ? (int)B * p->n_inputs : 0;
+    if (p->n_weights + n_gx > 0) {
         hipEvent_t ev = prof_begin(p, s);
         const int64_t nch1 = p->opts.method == QSV_METHOD_PER_GATE && !p->multi ? nch : 0;
-        // partials of a weight: per gate it drives (one, mostly), B times its chunks
         int64_t most = nch1;
         for (int32_t v : p->nchv) most = nch1 ? most : std::max<int64_t>(most, v);
-        const bool few = B * most <= 512;
-        hipLaunchKernelGGL(few ? k_grad_reduce<64> : k_grad_reduce<256>, dim3((unsigned)(few ? (n_out + 3) / 4 : n_out)),
-                           dim3(256), 0, s, (const double*)part, T->grad_csr, p->n_weights, p->n_inputs, n_out, (int)B,
-                           (const int64_t*)T->pu, (const int32_t*)T->nchv, gw, gx, w, (int)p->opts.weight_remap, nch1);
+        // threads per output by its partials (per gate it drives, one mostly): B * most of a
+        // weight, `most` of an input, whose threads also have their neighbours to fill a wave
+        const int nw = B * most <= 512 ? 64 : 256, ni = most <= 8 ? 1 : most <= 512 ? 64 : 256;
+        const int wb = (p->n_weights + 256 / nw - 1) / (256 / nw), xb = (n_gx + 256 / ni - 1) / (256 / ni);
+        auto* k = nw == 64 ? (ni == 1 ? k_grad_reduce<64, 1> : ni == 64 ? k_grad_reduce<64, 64> : k_grad_reduce<64, 256>)
+                           : (ni == 1 ? k_grad_reduce<256, 1> : ni == 64 ? k_grad_reduce<256, 64> : k_grad_reduce<256, 256>);
+        hipLaunchKernelGGL(k, dim3((unsigned)(wb + xb)), dim3(256), 0, s, (const double*)part, T->grad_csr, p->n_weights,
+                           p->n_inputs, wb, (int)B, (const int64_t*)T->pu, (const int32_t*)T->nchv, gw, gx, w,
+                           (int)p->opts.weight_remap, nch1);
         prof_end(p, s, ev, K_GRAD_REDUCE, 8.0 * (double)std::max<int64_t>(p->pu_total, 1) * B, 0.0);
     }
     HIP_TRY(hipGetLastError());
