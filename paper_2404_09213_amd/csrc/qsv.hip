@@ -241,6 +241,46 @@ struct CoefIn {
     int n_inputs, remap;
 };
 
+// Every product below is spelled out in multiply-adds, so that the two forms of k_coef and
+// every recipe of one core round alike, however each is compiled: results do not
+// depend on the form, and where an entry of a core is rounding noise its phase
+// comes out the same in P, Q and phi.
+__device__ __forceinline__ double2 zmul(double2 a, double2 b) {
+    return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
+}
+__device__ __forceinline__ double2 zconj(double2 a) { return make_double2(a.x, -a.y); }
+
+// matrix of gate D at sample b
+__device__ __forceinline__ void coef_gate(const CoefIn& in, const DGate& D, int b, double (&G)[8]) {
+    double th = 0.0;
+    if (D.src == QSV_SRC_WEIGHT) {
+        th = (double)in.weights[D.idx];
+        if (in.remap) th = M_PI * tanh(th);  // weight remapping into (-pi, pi)
+    } else if (D.src == QSV_SRC_INPUT) {
+        th = (double)in.inputs[(size_t)b * in.n_inputs + D.idx];
+    }
+    double s, c;
+    sincos(0.5 * th, &s, &c);
+    for (int e = 0; e < 8; ++e) G[e] = fma(s, D.S[e], fma(c, D.A[e], D.C[e]));
+}
+
+__device__ __forceinline__ void coef_identity(double (&M)[8]) {
+    for (int e = 0; e < 8; ++e) M[e] = e == 0 || e == 6 ? 1.0 : 0.0;
+}
+
+// M <- g * M (later gates act on the left)
+__device__ __forceinline__ void coef_mul(const double (&g)[8], double (&M)[8]) {
+    double N[8];
+    for (int row = 0; row < 2; ++row)
+        for (int col = 0; col < 2; ++col) {
+            const double ar = g[4 * row], ai = g[4 * row + 1], br = g[4 * row + 2], bi = g[4 * row + 3];
+            const double xr = M[2 * col], xi = M[2 * col + 1], yr = M[2 * col + 4], yi = M[2 * col + 5];
+            N[4 * row + 2 * col] = fma(ar, xr, fma(-ai, xi, fma(br, yr, -(bi * yi))));
+            N[4 * row + 2 * col + 1] = fma(ar, xi, fma(ai, xr, fma(br, yi, bi * yr)));
+        }
+    for (int e = 0; e < 8; ++e) M[e] = N[e];
+}
+
 // v of lane J of this lane's quad
 template <int J>
 __device__ __forceinline__ double quad_lane(double v) {
@@ -253,49 +293,35 @@ __device__ __forceinline__ double quad_lane(double v) {
 // M <- G * M for the gate matrix G held by lane J of the quad
 template <int J>
 __device__ __forceinline__ void coef_step(const double (&G)[8], double (&M)[8]) {
-    double g[8], N[8];
+    double g[8];
     for (int e = 0; e < 8; ++e) g[e] = quad_lane<J>(G[e]);
-    for (int row = 0; row < 2; ++row)
-        for (int col = 0; col < 2; ++col) {
-            double re = 0, im = 0;
-            for (int k = 0; k < 2; ++k) {
-                const double ar = g[(row * 2 + k) * 2], ai = g[(row * 2 + k) * 2 + 1];
-                const double br = M[(k * 2 + col) * 2], bi = M[(k * 2 + col) * 2 + 1];
-                re += ar * br - ai * bi;
-                im += ar * bi + ai * br;
-            }
-            N[(row * 2 + col) * 2] = re;
-            N[(row * 2 + col) * 2 + 1] = im;
-        }
-    for (int e = 0; e < 8; ++e) M[e] = N[e];
+    coef_mul(g, M);
 }
 
 // M <- the ordered product of `count` gates (recipe_gates[first ..]) at sample b,
 // evaluated by a quad of lanes: each takes one gate's matrix, then all four
-// form the product (later gates act on the left). n: the wave's largest count.
+// form the product. n: the wave's largest count.
 __device__ __forceinline__ void coef_product(const CoefIn& in, int first, int count, int n, int b, double (&M)[8]) {
     const int q = threadIdx.x & 3;
-    for (int e = 0; e < 8; ++e) M[e] = e == 0 || e == 6 ? 1.0 : 0.0;
+    coef_identity(M);
     for (int i0 = 0; i0 < n; i0 += 4) {
         double G[8];
-        for (int e = 0; e < 8; ++e) G[e] = e == 0 || e == 6 ? 1.0 : 0.0;
-        if (i0 + q < count) {
-            const DGate& D = in.gates[in.rg[first + i0 + q]];
-            double th = 0.0;
-            if (D.src == QSV_SRC_WEIGHT) {
-                th = (double)in.weights[D.idx];
-                if (in.remap) th = M_PI * tanh(th);  // weight remapping into (-pi, pi)
-            } else if (D.src == QSV_SRC_INPUT) {
-                th = (double)in.inputs[(size_t)b * in.n_inputs + D.idx];
-            }
-            double s, c;
-            sincos(0.5 * th, &s, &c);
-            for (int e = 0; e < 8; ++e) G[e] = D.C[e] + c * D.A[e] + s * D.S[e];
-        }
+        coef_identity(G);
+        if (i0 + q < count) coef_gate(in, in.gates[in.rg[first + i0 + q]], b, G);
         coef_step<0>(G, M);
         if (n > i0 + 1) coef_step<1>(G, M);
         if (n > i0 + 2) coef_step<2>(G, M);
         if (n > i0 + 3) coef_step<3>(G, M);
+    }
+}
+
+// The same by one lane; first and count are the same for the whole wave.
+__device__ __forceinline__ void coef_product1(const CoefIn& in, int first, int count, int b, double (&M)[8]) {
+    coef_identity(M);
+    for (int i = 0; i < count; ++i) {
+        double G[8];
+        coef_gate(in, in.gates[in.rg[first + i]], b, G);
+        coef_mul(G, M);
     }
 }
 
@@ -308,29 +334,79 @@ struct CoreParts {
 __device__ __forceinline__ CoreParts coef_core(const double (&M)[8], int core) {
     CoreParts o;
     o.p0 = o.p1 = o.q1 = make_double2(1.0, 0.0);
-    double c, s;
-    if (core != CORE_GEN) {  // no core: nothing of it is used
-        c = 1.0;
-        s = 0.0;
-    } else {
-        const double2 a = make_double2(M[0], M[1]), d = make_double2(M[4], M[5]);
-        c = sqrt(a.x * a.x + a.y * a.y);
-        s = sqrt(d.x * d.x + d.y * d.y);
-        // below 1e-10 an entry's phase cannot matter in float32
-        if (c > 1e-10 || !(c == c)) o.p0 = make_double2(a.x / c, a.y / c);
-        if (s > 1e-10 || !(s == s)) o.p1 = make_double2(d.x / s, d.y / s);
-        // q1 = det U / (p0 p1), which makes p0 q1 (-s) and p1 q1 c the other two entries
-        const double2 det = make_double2(M[0] * M[6] - M[1] * M[7] - (M[2] * M[4] - M[3] * M[5]),
-                                         M[0] * M[7] + M[1] * M[6] - (M[2] * M[5] + M[3] * M[4]));
-        const double2 pp = cmul(o.p0, o.p1);
-        const double2 q = cmul(det, make_double2(pp.x, -pp.y));
-        const double n = sqrt(q.x * q.x + q.y * q.y);
-        o.q1 = make_double2(q.x / n, q.y / n);
-    }
-    if (c < 0.0) c = -c, s = -s;
+    o.a = o.b = 0.0;
+    if (core != CORE_GEN) return o;  // no core: nothing of it is used
+    const double c = sqrt(fma(M[0], M[0], M[1] * M[1])), s = sqrt(fma(M[4], M[4], M[5] * M[5]));
+    // below 1e-10 an entry's phase cannot matter in float32
+    if (c > 1e-10 || !(c == c)) o.p0 = make_double2(M[0] / c, M[1] / c);
+    if (s > 1e-10 || !(s == s)) o.p1 = make_double2(M[4] / s, M[5] / s);
+    // q1 = det U / (p0 p1), which makes p0 q1 (-s) and p1 q1 c the other two entries
+    const double2 det = make_double2(fma(M[0], M[6], fma(-M[1], M[7], fma(-M[2], M[4], M[3] * M[5]))),
+                                     fma(M[0], M[7], fma(M[1], M[6], fma(-M[2], M[5], -(M[3] * M[4])))));
+    const double2 q = zmul(det, zconj(zmul(o.p0, o.p1)));
+    const double n = sqrt(fma(q.x, q.x, q.y * q.y));
+    o.q1 = make_double2(q.x / n, q.y / n);
     o.a = s / (1.0 + c);
     o.b = s;
     return o;
+}
+
+// f1 / f0 of a diagonal factor, from its gates' product C and its core's parts
+__device__ __forceinline__ double2 coef_factor(const DFactor& F, const double (&C)[8], const CoreParts& P) {
+    double2 f0 = make_double2(1.0, 0.0), f1 = P.q1;
+    if (F.kind == F_DIAG) {
+        f0 = make_double2(C[0], C[1]);
+        f1 = make_double2(C[6], C[7]);
+    } else if (F.kind == F_POST) {
+        f0 = P.p0;
+        f1 = P.p1;
+    }
+    f1 = zmul(f1, zconj(f0));
+    if (F.dagger) f1.y = -f1.y;
+    return f1;
+}
+
+// Stores a single-value recipe. C: the product of its gates (of its core's, for
+// RC_VMAT, whose own product is A), P: its core's parts.
+template <class R>
+__device__ __forceinline__ void coef_store(const DRecipe& Rc, const double (&C)[8], double (&A)[8], const CoreParts& P,
+                                           R* __restrict__ dst) {
+    if (Rc.kind == RC_SHEAR) {
+        dst[0] = (R)(Rc.dagger ? -P.a : P.a);  // R(phi)^dagger = R(-phi)
+        dst[1] = (R)(Rc.dagger ? -P.b : P.b);
+        return;
+    }
+    if (Rc.kind == RC_VMAT) {
+        for (int col = 0; col < 2; ++col) {
+            const double2 u = zmul(zconj(P.p0), make_double2(A[2 * col], A[2 * col + 1]));
+            const double2 v = zmul(zconj(P.p1), make_double2(A[4 + 2 * col], A[5 + 2 * col]));
+            A[2 * col] = u.x;
+            A[2 * col + 1] = u.y;
+            A[4 + 2 * col] = v.x;
+            A[5 + 2 * col] = v.y;
+        }
+    } else {
+        for (int e = 0; e < 8; ++e) A[e] = C[e];
+    }
+    if (Rc.dagger) {
+        dst[0] = (R)A[0]; dst[1] = (R)-A[1];  // m00*
+        dst[2] = (R)A[4]; dst[3] = (R)-A[5];  // m10*
+        dst[4] = (R)A[2]; dst[5] = (R)-A[3];  // m01*
+        dst[6] = (R)A[6]; dst[7] = (R)-A[7];  // m11*
+    } else {
+        for (int e = 0; e < 8; ++e) dst[e] = (R)A[e];
+    }
+}
+
+// Stores entry k of a RC_DVEC recipe, and what rounding took off it.
+template <class R>
+__device__ __forceinline__ void coef_store_entry(const DRecipe& Rc, int k, double2 D, R* __restrict__ dst) {
+    dst[2 * k] = (R)D.x;
+    dst[2 * k + 1] = (R)D.y;
+    if (Rc.core) {
+        dst[32 + 2 * k] = (R)(D.x - (double)(R)D.x);
+        dst[33 + 2 * k] = (R)(D.y - (double)(R)D.y);
+    }
 }
 
 __device__ __forceinline__ int wave_max(int v) {
@@ -339,16 +415,50 @@ __device__ __forceinline__ int wave_max(int v) {
     return __builtin_amdgcn_readfirstlane(v);
 }
 
-// Values of a plan's recipes for one call (see RecipeKind). A wave takes 16
-// single-value recipes, one per quad of lanes, or one 16-entry vector, whose
-// factors its quads evaluate side by side. n1 / n2 single values and vectors
-// are shared by the batch, p1 / p2 are per sample. A chain of dependent
-// loads, one sine and cosine and a few products bounds it, so every angle of a
-// list has a lane of its own (one thread per recipe, gate after gate, takes 3-8
-// times as long for the vectors). P, Q and phi of one core are evaluated by
-// different waves: by the same instructions, so that where an entry of U is
-// rounding noise its phase still comes out the same everywhere.
-template <class R>  // R: matrix entry type (float, or double for complex128 states)
+// One recipe for 64 samples, a sample per lane: the recipe, its gates and every branch
+// are the wave's, and every lane works, on one angle after the other.
+template <class R>
+__device__ __forceinline__ void coef_samples(const CoefIn& in, const DRecipe& Rc, const DFactor* __restrict__ factors,
+                                             int b, bool on, R* __restrict__ dst) {
+    double C[8], A[8];
+    if (Rc.kind != RC_DVEC) {
+        const bool vmat = Rc.kind == RC_VMAT;
+        coef_product1(in, vmat ? Rc.first2 : Rc.first, vmat ? Rc.count2 : Rc.count, b, C);
+        if (vmat) coef_product1(in, Rc.first, Rc.count, b, A);
+        if (on) coef_store(Rc, C, A, coef_core(C, Rc.core), dst);
+        return;
+    }
+    double2 F[kRegBits];
+    for (int p = 0; p < kRegBits; ++p) F[p] = make_double2(1.0, 0.0);
+    for (int i = 0; i < Rc.count; ++i) {
+        const DFactor& X = factors[Rc.first + i];
+        coef_product1(in, X.first, X.count, b, C);
+        const double2 f = coef_factor(X, C, coef_core(C, X.core));
+#pragma unroll
+        for (int p = 0; p < kRegBits; ++p)
+            if (X.pos == p) F[p] = zmul(F[p], f);
+    }
+    if (!on) return;
+    double2 D[kRegs];
+    D[0] = make_double2(1.0, 0.0);
+#pragma unroll
+    for (int p = 0; p < kRegBits; ++p)
+        for (int k = 0; k < 1 << p; ++k) D[k | 1 << p] = zmul(D[k], F[p]);
+    for (int k = 0; k < kRegs; ++k) coef_store_entry(Rc, k, D[k], dst);
+}
+
+// Values of a plan's recipes for one call (see RecipeKind). n1 / n2 single values and
+// 16-entry vectors are shared by the batch, p1 / p2 are per sample.
+//
+// A wave takes 16 single-value recipes, one per quad of lanes, or one vector, whose
+// factors its quads evaluate side by side. A chain of dependent loads, one sine
+// and cosine and a few products bounds it, so every angle of a list has a lane of
+// its own (one thread per recipe, gate after gate, takes 3-8 times as long for the vectors).
+//
+// SAMPLES: the per-sample recipes by coef_samples() instead, where the quads' waves are
+// more than the chip holds: most of their lanes idle (few lists have four angles, few
+// samples 16 recipes), and they are bound by arithmetic then.
+template <class R, bool SAMPLES>  // R: matrix entry type (float, or double for complex128 states)
 __global__ __launch_bounds__(64) void k_coef(CoefIn in, const DRecipe* __restrict__ recipes,
                                              const DFactor* __restrict__ factors, int n1, int n2, int p1, int p2,
                                              int B, int n_shared, int n_ps, R* __restrict__ mats) {
@@ -362,11 +472,21 @@ __global__ __launch_bounds__(64) void k_coef(CoefIn in, const DRecipe* __restric
         k = (int)g - gs;
     } else {
         g -= gs + n2;
-        if (gp + p2 == 0) return;
-        b = (int)(g / (gp + p2));
-        if (b >= B) return;
-        k = (int)(g % (gp + p2));
+        const int per = SAMPLES ? p1 + p2 : gp + p2;
+        if (per == 0) return;
+        b = (int)(g / per);
+        k = (int)(g % per);
         first = n1 + n2;
+        if (SAMPLES) {
+            b = b * 64 + lane;
+            if (b - lane >= B) return;
+            const DRecipe Rc = recipes[first + k];
+            const int bb = min(b, B - 1);
+            coef_samples(in, Rc, factors, bb, b < B,
+                         mats + 8 * ((size_t)n_shared + (size_t)bb * n_ps + (size_t)(-Rc.out - 1)));
+            return;
+        }
+        if (b >= B) return;
         lim = p1;
         g = k;
         k -= gp;
@@ -378,85 +498,38 @@ __global__ __launch_bounds__(64) void k_coef(CoefIn in, const DRecipe* __restric
     if (on) Rc = recipes[first + r];
     R* dst = Rc.out >= 0 ? mats + 8 * (size_t)Rc.out
                          : mats + 8 * ((size_t)n_shared + (size_t)b * n_ps + (size_t)(-Rc.out - 1));
-    double2 D = make_double2(1.0, 0.0);
-    const int chunks = vec ? (Rc.count + 15) / 16 : 1;
-    for (int ch = 0; ch < chunks; ++ch) {
-        // this quad's gate list (the core's, for a RC_VMAT, whose product comes second)
-        int first1 = Rc.first, count1 = Rc.count, core = Rc.core;
-        DFactor F{};
-        if (vec) {
-            if (ch * 16 + quad < Rc.count) F = factors[Rc.first + ch * 16 + quad];
-            first1 = F.first;
-            count1 = F.count;
-            core = F.core;
-        } else if (Rc.kind == RC_VMAT) {
-            first1 = Rc.first2;
-            count1 = Rc.count2;
-        }
-        double A[8], C[8];
-        coef_product(in, first1, count1, wave_max(count1), b, C);
-        const CoreParts P = coef_core(C, core);
-        if (vec) {
-            double2 f0 = make_double2(1.0, 0.0), f1 = f0;
-            if (F.kind == F_DIAG) {
-                f0 = make_double2(C[0], C[1]);
-                f1 = make_double2(C[6], C[7]);
-            } else if (F.kind == F_POST) {
-                f0 = P.p0;
-                f1 = P.p1;
-            } else {
-                f1 = P.q1;
-            }
-            f1 = cmul(f1, make_double2(f0.x, -f0.y));
-            if (F.dagger) f1.y = -f1.y;
-            if ((lane & 3) == 0) {
-                fac[quad] = f1;
-                fpos[quad] = F.pos;
-            }
-            __syncthreads();
-            const int n = min(16, Rc.count - ch * 16);
-            for (int j = 0; j < n; ++j)
-                if ((lane >> fpos[j]) & 1) D = cmul(D, fac[j]);
-            __syncthreads();
-            continue;
-        }
+    double C[8];
+    if (!vec) {
         const bool vmat = Rc.kind == RC_VMAT;
-        coef_product(in, Rc.first, vmat ? Rc.count : 0, wave_max(vmat ? Rc.count : 0), b, A);
-        if (!on || (lane & 3)) return;
-        if (Rc.kind == RC_SHEAR) {
-            dst[0] = (R)(Rc.dagger ? -P.a : P.a);  // R(phi)^dagger = R(-phi)
-            dst[1] = (R)(Rc.dagger ? -P.b : P.b);
-            return;
-        }
-        if (vmat) {
-            for (int col = 0; col < 2; ++col) {
-                const double2 u = cmul(make_double2(P.p0.x, -P.p0.y), make_double2(A[2 * col], A[2 * col + 1]));
-                const double2 v = cmul(make_double2(P.p1.x, -P.p1.y), make_double2(A[4 + 2 * col], A[5 + 2 * col]));
-                A[2 * col] = u.x;
-                A[2 * col + 1] = u.y;
-                A[4 + 2 * col] = v.x;
-                A[5 + 2 * col] = v.y;
-            }
-        } else {
-            for (int e = 0; e < 8; ++e) A[e] = C[e];
-        }
-        if (Rc.dagger) {
-            dst[0] = (R)A[0]; dst[1] = (R)-A[1];  // m00*
-            dst[2] = (R)A[4]; dst[3] = (R)-A[5];  // m10*
-            dst[4] = (R)A[2]; dst[5] = (R)-A[3];  // m01*
-            dst[6] = (R)A[6]; dst[7] = (R)-A[7];  // m11*
-        } else {
-            for (int e = 0; e < 8; ++e) dst[e] = (R)A[e];
-        }
+        const int c1 = vmat ? Rc.count2 : Rc.count, c2 = vmat ? Rc.count : 0;
+        double A[8];
+        coef_product(in, vmat ? Rc.first2 : Rc.first, c1, wave_max(c1), b, C);
+        coef_product(in, Rc.first, c2, wave_max(c2), b, A);
+        if (on && !(lane & 3)) coef_store(Rc, C, A, coef_core(C, Rc.core), dst);
+        return;
     }
-    if (vec && lane < 16) {
-        dst[2 * lane] = (R)D.x;
-        dst[2 * lane + 1] = (R)D.y;
-        if (Rc.core) {  // what rounding took off
-            dst[32 + 2 * lane] = (R)(D.x - (double)(R)D.x);
-            dst[33 + 2 * lane] = (R)(D.y - (double)(R)D.y);
+    double2 D = make_double2(1.0, 0.0);  // lane p < 4: the factors on register position p
+    for (int c0 = 0; c0 < Rc.count; c0 += 16) {
+        DFactor F{};
+        if (c0 + quad < Rc.count) F = factors[Rc.first + c0 + quad];
+        coef_product(in, F.first, F.count, wave_max(F.count), b, C);
+        const double2 f = coef_factor(F, C, coef_core(C, F.core));
+        if ((lane & 3) == 0) {
+            fac[quad] = f;
+            fpos[quad] = F.pos;
         }
+        __syncthreads();
+        const int n = min(16, Rc.count - c0);
+        for (int j = 0; j < n; ++j)
+            if (fpos[j] == lane) D = zmul(D, fac[j]);
+        __syncthreads();
     }
+    if (lane < kRegBits) fac[lane] = D;
+    __syncthreads();
+    D = make_double2(1.0, 0.0);
+    for (int p = 0; p < kRegBits; ++p)
+        if (lane >> p & 1) D = zmul(D, fac[p]);
+    if (lane < kRegs) coef_store_entry(Rc, lane, D, dst);
 }
 
 // ----------------------------------------------------------------------------
@@ -2376,6 +2449,14 @@ int check_plan(const qsv_plan_t* p) {
     return QSV_OK;
 }
 
+// Waves of quads above which per-sample recipes go by sample (see k_coef). A launch by
+// sample takes at least as long as its longest list (6 to 23 us, 50 for lists of 20 angles),
+// one by quads 6 to 10 us plus 1.5 to 3 us per 1,024 waves. They meet at 3,000 to
+// 5,000 waves where lists are short, 8,000 to 11,000 where runs of three rotations
+// alternate with controlled gates (8 qubits, both directions' data re-uploaded, backward: batch 256
+// 15 against 23 us, 700 29 against 23, 8,192 255 against 52).
+constexpr int64_t kCoefWaves = 8192;
+
 int run_coef(const qsv_plan_t* p, DeviceTables* T, int dir, const float* w, const float* x, int64_t B,
              float* mats, hipStream_t s) {
     const int* n = p->n_recipe_cls[dir];
@@ -2383,15 +2464,21 @@ int run_coef(const qsv_plan_t* p, DeviceTables* T, int dir, const float* w, cons
     const int nsh = p->n_shared_mats[dir], nps = p->n_ps_mats[dir];
     const DRecipe* rec = T->recipes;
     for (int i = 0; i < 4; ++i) rec += dir ? p->n_recipe_cls[0][i] : 0;
-    const int64_t waves = (n[0] + 15) / 16 + n[1] + B * ((n[2] + 15) / 16 + n[3]);
+    const int64_t shared = (n[0] + 15) / 16 + n[1], quads = B * ((n[2] + 15) / 16 + n[3]);
+    const int64_t by_sample = (B + 63) / 64 * (n[2] + n[3]);
+    const bool samples = quads > kCoefWaves;
+    const int64_t waves = shared + (samples ? by_sample : quads);
     const CoefIn in = {T->gates, T->recipe_gates, w, x, p->n_inputs, (int)p->opts.weight_remap};
     hipEvent_t ev = prof_begin(p, s);
-    if (c128(p))
-        hipLaunchKernelGGL(k_coef<double>, grid_1d(waves), dim3(64), 0, s, in, rec, T->factors,
-                           n[0], n[1], n[2], n[3], (int)B, nsh, nps, (double*)mats);
-    else
-        hipLaunchKernelGGL(k_coef<float>, grid_1d(waves), dim3(64), 0, s, in, rec, T->factors,
-                           n[0], n[1], n[2], n[3], (int)B, nsh, nps, mats);
+    if (c128(p)) {
+        auto* k = samples ? k_coef<double, true> : k_coef<double, false>;
+        hipLaunchKernelGGL(k, grid_1d(waves), dim3(64), 0, s, in, rec, T->factors, n[0], n[1], n[2], n[3], (int)B, nsh,
+                           nps, (double*)mats);
+    } else {
+        auto* k = samples ? k_coef<float, true> : k_coef<float, false>;
+        hipLaunchKernelGGL(k, grid_1d(waves), dim3(64), 0, s, in, rec, T->factors, n[0], n[1], n[2], n[3], (int)B, nsh,
+                           nps, mats);
+    }
     prof_end(p, s, ev, K_COEF, 4.0 * (double)amp_size(p) * ((double)nsh + (double)B * nps),
              0.0);
     HIP_TRY(hipGetLastError());

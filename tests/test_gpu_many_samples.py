@@ -66,10 +66,10 @@ def test_gradient_sums(n, batch, opts):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kernel", ["k_grad_reduce"])
+@pytest.mark.parametrize("kernel", ["k_grad_reduce", "k_coef"])
 def test_passes_take_most_of_a_step(kernel):
     """8 qubits, batch 8192, every gate run per sample: one block per input gradient took 2.7 times
-    as long as the backward pass."""
+    as long as the backward pass, coefficients by quads of lanes 4 times as long."""
     import torch
     c = reuploading(8, 5)
     plan = _plan(c)
@@ -86,3 +86,40 @@ def test_passes_take_most_of_a_step(kernel):
     passes = sum(v for k, v in best.items() if k.startswith("qsv_"))
     print({k: round(1e3 * v, 1) for k, v in best.items()})
     assert best[kernel] < passes
+
+
+def _mixed(n, gates, n_inputs, p_input):
+    return I.random_mixed(n, gates, np.random.default_rng(n), n_inputs=n_inputs, p_input=p_input, kinds=I.ALL_KINDS)
+
+
+# (circuit, batch, options): coefficients by quads in pieces of 16 samples, by sample in
+# the whole batch, whose last 64 samples are not all there
+FORMS = [("reup4", lambda: reuploading(4, 4), 4001, {}),
+         ("reup8", lambda: reuploading(8, 5), 1000, {}),
+         ("reup13", lambda: reuploading(13, 2), 1001, {}),
+         ("mixed5", lambda: _mixed(5, 150, 5, 1.0), 3003, {}),
+         ("mixed9_remap", lambda: _mixed(9, 200, 3, 0.5), 2049, {"weight_remap": 1}),
+         ("ladder_tables", lambda: I.rx_ry_rz_cz_ladder(5, 2), 9000, {"codegen": 0}),
+         ("mixed_tables", lambda: _mixed(6, 120, 6, 0.7), 2100, {"codegen": 0}),
+         ("plain", lambda: _mixed(5, 150, 5, 0.8), 1300, {"method": "per_gate"}),
+         ("plain_c128", lambda: _mixed(4, 150, 4, 0.8), 1290, {"method": "per_gate", "amp_dtype": "c128"})]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,make,batch,opts", FORMS, ids=[f[0] for f in FORMS])
+def test_coefficients_do_not_depend_on_the_batch(name, make, batch, opts):
+    """Both forms of the coefficients' kernel round alike: states, expectations and (where the
+    partials' chunks are the same) input gradients agree bit for bit."""
+    import torch
+    print(f"[coefficients] {name}", flush=True)
+    c = make()
+    plan = _plan(c, **opts)
+    w, x, g = _data(c, batch, 21)
+    state, E = plan.forward_expval(w, x, batch)
+    gw, gx = plan.backward(w, x, state, g)
+    for b in list(range(0, batch, 16 * max(1, batch // 160))) + [batch - 1 - (batch - 1) % 16]:
+        s = slice(b, min(b + 16, batch))
+        st, e = plan.forward_expval(w, x[s].contiguous(), s.stop - b)
+        assert torch.equal(st, state[s]) and torch.equal(e, E[s]), b
+        dw, dx = plan.backward(w, x[s].contiguous(), st, g[s].contiguous())
+        assert torch.equal(dx, gx[s]) if "method" not in opts else (dx - gx[s]).abs().max().item() <= 1e-5 * c.n_qubits, b
