@@ -842,8 +842,43 @@ struct Waiting {
     explicit Waiting(int W) : diag(W) {}
 };
 
+// Vector instructions per amplitude (of psi and lambda together) that a generated backward pass
+// takes, about. Within 3% of the compiled counts' ratio of the two forms of a pass (25 passes of rings,
+// ladders and random circuits of 5 to 20 qubits).
+double pass_instrs(const qsv_plan_t* p, const DPass& ps) {
+    double f = 0.0;
+    for (int s = ps.stage0; s < ps.stage0 + ps.n_stages; ++s) {
+        f += 10.0;  // the exchange before it
+        for (int i = p->stages[s].op0; i < p->stages[s].op1; ++i) {
+            const DOp& o = p->ops[i];
+            // a control in the registers leaves half of them out, one outside adds selects
+            double half = 1.0, sel = 0.0;
+            for (int c : {o.ctl, o.ctl2}) {
+                if (c >= kCtlNonReg) sel = 4.0;
+                else if (c >= 0) half *= 0.5;
+            }
+            const double bits = 1.0 - 1.0 / (double)(1 << popc((uint32_t)o.pos & 15u));
+            switch (o.kind) {
+            case OP_U2: f += (16.0 + sel) * half; break;
+            case OP_REAL: case OP_RXL: case OP_DIAG: f += (8.0 + sel) * half; break;
+            case OP_GX: case OP_GY: case OP_GZ: f += 2.0 * half; break;
+            case OP_SIGN: f += 4.0; break;
+            case OP_SWAP: f += sel * half; break;
+            case OP_SHEAR: f += 6.0; break;
+            case OP_DVEC: f += 8.0 * bits; break;
+            case OP_DVEC2: f += 16.0 * bits; break;
+            default: break;
+            }
+        }
+    }
+    return f;
+}
+
 // Builds one DPass (tile qubits + stages + ops) from a pass's gate list.
 struct PassBuilder {
+    // cores have to save this much: their coefficients take more (5 us of a launch where many are per
+    // sample), and products round better
+    static constexpr double kCoresWorth = 0.97;
     qsv_plan_t* p;
     bool backward;
     // backward: first gate (program order) on each qubit. A unit holding the
@@ -886,8 +921,55 @@ struct PassBuilder {
         for (int i = 0; i < kRegBits; ++i) ps.nat_gr[i] = 1 << ps.lq[ps.nat.reg[i]];
     }
 
+    // What a pass appends to the plan, so that it can be taken back.
+    struct Mark {
+        size_t stages, ops, terms, gouts, recipes, recipe_gates, factors, out, order;
+        int n_shared, n_ps;
+    };
+    Mark mark(const std::vector<DPass>& out, const std::vector<int32_t>& order) const {
+        return {p->stages.size(), p->ops.size(), p->terms.size(), p->gouts.size(), p->recipes.size(), p->recipe_gates.size(),
+                p->factors.size(), out.size(), order.size(), p->n_shared_mats[p->dir], p->n_ps_mats[p->dir]};
+    }
+    void take_back(const Mark& k, std::vector<DPass>& out, std::vector<int32_t>& order) {
+        p->stages.resize(k.stages);
+        p->ops.resize(k.ops);
+        p->terms.resize(k.terms);
+        p->gouts.resize(k.gouts);
+        p->recipes.resize(k.recipes);
+        p->recipe_gates.resize(k.recipe_gates);
+        p->factors.resize(k.factors);
+        out.resize(k.out);
+        order.resize(k.order);
+        p->n_shared_mats[p->dir] = k.n_shared;
+        p->n_ps_mats[p->dir] = k.n_ps;
+    }
+
+    // A backward pass of the generated kernels takes its 1-qubit runs as rotation cores
+    // (see CoreKind) where that saves instructions, else each as one 2x2 product. Cores win where runs of
+    // rotations meet on several qubits (a ladder's passes take 0.71 to 0.77 of the
+    // instructions, a ring's 0.82 to 0.86); where single gates alternate with controlled
+    // ones (random circuits: 0.94 to 1.17), nothing is gathered, and what a run loses by being
+    // taken apart shows (16 qubits, batch 256: 120 random gates, backward 421 us with cores,
+    // 355 with products; four layers of a ladder 410 against 557).
     void build(const std::vector<int>& gates, uint32_t dense, int m, int c, int flags,
                std::vector<DPass>& out, std::vector<int32_t>& order) {
+        if (!backward || !p->opts.codegen) {
+            emit(gates, dense, m, c, flags, false, out, order);
+            return;
+        }
+        const Mark at = mark(out, order);
+        emit(gates, dense, m, c, flags, true, out, order);
+        const double with_cores = pass_instrs(p, out.back());
+        take_back(at, out, order);
+        emit(gates, dense, m, c, flags, false, out, order);
+        const double without = pass_instrs(p, out.back());
+        if (with_cores > kCoresWorth * without) return;
+        take_back(at, out, order);
+        emit(gates, dense, m, c, flags, true, out, order);
+    }
+
+    void emit(const std::vector<int>& gates, uint32_t dense, int m, int c, int flags, bool cores,
+              std::vector<DPass>& out, std::vector<int32_t>& order) {
         const int W = p->W;
         DPass ps;
         std::memset(&ps, 0, sizeof ps);
@@ -904,7 +986,6 @@ struct PassBuilder {
             else { local_of_qubit[q] = -1; ps.oq[k++] = W - 1 - q; }
         }
         const bool fuse = !p->opts.bwd_gate_by_gate;
-        const bool cores = backward && p->opts.codegen != 0;  // rotation cores
         std::vector<Unit> units = cores ? bwd_core_units(p, gates, fuse) : backward ? bwd_units(p, gates, fuse)
                                                                                      : fwd_units(p, gates);
         auto groups = group_stages(units);
@@ -1170,7 +1251,9 @@ struct PassBuilder {
                         }
                 sign_op = -1;
                 // the unit's op; a table-driven backward takes its components (X, Y, Z
-                // in consecutive slots) in the same op, before applying it
+                // in consecutive slots) in the same op, before applying it, a generated one in
+                // ops of their own
+                const bool own_comps = p->opts.codegen != 0;
                 DOp o;
                 std::memset(&o, 0, sizeof o);
                 o.pos = pos_of(U.qubit);
@@ -1185,10 +1268,12 @@ struct PassBuilder {
                     // chain: X/Y/Z components after the chain, one output per
                     // parametric gate, then the chain's product uncomputed at once
                     int slot_of[3] = {-1, -1, -1};
-                    o.comps = U.comps;
-                    o.slot = nslot;
+                    if (!own_comps) {
+                        o.comps = U.comps;
+                        o.slot = nslot;
+                    }
                     for (int a = 0; a < 3; ++a)
-                        if (U.comps >> a & 1) slot_of[a] = nslot++;
+                        if (U.comps >> a & 1) slot_of[a] = own_comps ? comp(U, OP_GX + a, -1, -1) : nslot++;
                     const int n = (int)U.gates.size();
                     for (int j = 0; j < n; ++j) {
                         const qsv_gate& Gj = p->gates[U.gates[j]];
@@ -1216,7 +1301,7 @@ struct PassBuilder {
                     if (G.src != QSV_SRC_NONE) {
                         const int axis = axis_of(G.kind == QSV_CRY ? QSV_RY : G.kind == QSV_CRZ ? QSV_RZ : G.kind);
                         int slot;
-                        if (cores) {
+                        if (own_comps) {
                             slot = comp(U, OP_GX + axis, o.ctl, o.ctl2);
                         } else {
                             o.comps = 1 << axis;
