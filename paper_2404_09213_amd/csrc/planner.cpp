@@ -843,14 +843,17 @@ struct Waiting {
 };
 
 // Vector instructions per amplitude (of psi and lambda together) that a generated backward pass
-// takes, about. Within 3% of the compiled counts' ratio of the two forms of a pass (25 passes of rings,
-// ladders and random circuits of 5 to 20 qubits).
+// takes, about: the ratio of a pass's two forms comes within 5% of that of the compiled counts (43
+// passes of rings, ladders and random circuits of 5 to 28 qubits).
 double pass_instrs(const qsv_plan_t* p, const DPass& ps) {
     double f = 0.0;
     for (int s = ps.stage0; s < ps.stage0 + ps.n_stages; ++s) {
         f += 10.0;  // the exchange before it
+        int nz = 0;  // Z components so far at this point: they share their products
         for (int i = p->stages[s].op0; i < p->stages[s].op1; ++i) {
             const DOp& o = p->ops[i];
+            if (!is_grad_op(o.kind)) nz = 0;
+            const bool joint = o.kind == OP_GZ && o.pos >= 0 && o.ctl < 0 && nz++;
             // a control in the registers leaves half of them out, one outside adds selects
             double half = 1.0, sel = 0.0;
             for (int c : {o.ctl, o.ctl2}) {
@@ -861,7 +864,7 @@ double pass_instrs(const qsv_plan_t* p, const DPass& ps) {
             switch (o.kind) {
             case OP_U2: f += (16.0 + sel) * half; break;
             case OP_REAL: case OP_RXL: case OP_DIAG: f += (8.0 + sel) * half; break;
-            case OP_GX: case OP_GY: case OP_GZ: f += 2.0 * half; break;
+            case OP_GX: case OP_GY: case OP_GZ: f += joint ? 0.8 : 2.0 * half; break;
             case OP_SIGN: f += 4.0; break;
             case OP_SWAP: f += sel * half; break;
             case OP_SHEAR: f += 6.0; break;
@@ -876,9 +879,6 @@ double pass_instrs(const qsv_plan_t* p, const DPass& ps) {
 
 // Builds one DPass (tile qubits + stages + ops) from a pass's gate list.
 struct PassBuilder {
-    // cores have to save this much: their coefficients take more (5 us of a launch where many are per
-    // sample), and products round better
-    static constexpr double kCoresWorth = 0.97;
     qsv_plan_t* p;
     bool backward;
     // backward: first gate (program order) on each qubit. A unit holding the
@@ -963,7 +963,10 @@ struct PassBuilder {
         take_back(at, out, order);
         emit(gates, dense, m, c, flags, false, out, order);
         const double without = pass_instrs(p, out.back());
-        if (with_cores > kCoresWorth * without) return;
+        // Near a tie either may win: random circuits' passes take 0.95 to 1.01 of the time with
+        // products, the last passes of a ring (estimate 1.01) fill 150 to 158 registers with
+        // them, one wave a SIMD less, against 110.
+        if (with_cores > 1.015 * without) return;
         take_back(at, out, order);
         emit(gates, dense, m, c, flags, true, out, order);
     }

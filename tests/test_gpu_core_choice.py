@@ -40,7 +40,7 @@ def _cores(plan):
     return binding.qsv_plan_codegen_source(plan.handle).count("a_ = M_[0], b_ = M_[1]")
 
 
-@pytest.mark.parametrize("n,gates,seed", [(16, 120, 16), (12, 120, 12), (6, 120, 6), (12, 120, 7)])
+@pytest.mark.parametrize("n,gates,seed", [(16, 120, 16), (12, 120, 12), (6, 120, 6), (9, 120, 7)])
 def test_random_circuits_keep_their_stages(n, gates, seed):
     """Taken apart, the runs of these circuits need a stage more, and more instructions."""
     c = I.random_mixed(n, gates, np.random.default_rng(seed), n_inputs=n, p_input=0.3, kinds=I.ALL_KINDS)
