@@ -423,8 +423,9 @@ int qsv_plan_codegen_check(const qsv_plan_t* plan, const char* arch);
  * the paper's method): the global loads and stores of pass `pass` of the
  * forward (which = 0) or backward (which = 1) schedule in a plain copy
  * kernel, with no arithmetic between them, on the arrays the pass itself
- * uses and through the same tiles, thread layout, 16-byte pairs and block
- * order as the pass kernel generated for it. A pass that takes about as long
+ * uses and through the same tiles, thread layout, 16-byte pairs, kind of access
+ * (non-temporal for large launches) and block order as the pass kernel
+ * generated for it. A pass that takes about as long
  * is bound by its accesses (it can also be faster: the copy issues every
  * tile's stores right behind its loads, the pass spreads them out).
  *   which = 0: reads and writes d_state (batch x 2^n complex64) in place,

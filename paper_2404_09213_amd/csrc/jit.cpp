@@ -990,7 +990,7 @@ private:
         // the thread index, shared by all accesses and by psi and lambda, plus a
         // scalar constant per access, no address arithmetic (pointers take two
         // 64-bit additions' worth of vector instructions each).
-        const bool buf = W_ <= 28;
+        const bool buf = W_ <= kMaxBufferQubits;
         auto open = [&](const std::string& name, const std::string& ptr) {
             return buf ? "const __amdgpu_buffer_rsrc_t " + name + "b_ = qsv_buf(" + ptr + ", " + I(8LL << W_) + "u); " : std::string();
         };
@@ -1002,7 +1002,7 @@ private:
         // them; 21 qubits, batch 7, forward: 760 -> 857 us).
         const bool nt = buf && v16;
         if (nt)
-            o_ << "  const bool nt_ = gridDim.x >= " << ((512u << 20) / ((8u << m_) * (unsigned)arrays_.size())) << "u;\n";
+            o_ << "  const bool nt_ = gridDim.x >= " << stream_tiles(m_, (int)arrays_.size()) << "u;\n";
         // by alignment (8 bytes: s1, 16: s2) and size (s3)
         auto by_access = [&](const std::string& ptr, const std::string& s1, const std::string& s2, const std::string& s3) {
             const std::string two = "if (((qsv_uptr)(" + ptr + ") & 15) != 0) { " + s1 + "} else ";

@@ -148,6 +148,12 @@ enum : int32_t {
 // linear over XOR.
 inline int swizzle(int l) { return l ^ (((l >> 5) ^ (l >> 10)) & 31); }
 
+// How a generated pass reaches its arrays: raw buffers where a sample's bytes fit 32
+// bits, and non-temporally (16-byte accesses) from as many tiles on as fill 512 MB in the
+// launch's arrays (1 or 2 states).
+constexpr int kMaxBufferQubits = 28;
+inline unsigned stream_tiles(int m, int arrays) { return (512u << 20) / ((8u << m) * (unsigned)arrays); }
+
 enum PassFlags : int32_t {
     PF_FIRST_BWD = 1,  // backward: read psi_N from the caller's state, build lambda on the fly
     PF_LAST_BWD = 2,   // backward: nothing is written back

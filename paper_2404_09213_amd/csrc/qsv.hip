@@ -2134,62 +2134,77 @@ __global__ __launch_bounds__(256) void k_expval_final_multi(const DCirc* __restr
 // between: the same tiles, 16 amplitudes per thread, register bits (tile bit 0
 // when it is amplitude bit 0, else the fourth-highest tile bit, plus the top
 // three), thread-index bits on the other tile bits in ascending order,
-// 16-byte pairs when tile bit 0 is amplitude bit 0, and the XCD-contiguous
-// block order. rd / wr: bit 0 array a, bit 1 array b (read from ra / rb,
+// 16-byte pairs when tile bit 0 is amplitude bit 0, the XCD-contiguous
+// block order, and the pass's kind of access (ACC: 0 pointers, 1 buffers, 2
+// non-temporal buffers, 16-byte pairs only). rd / wr: bit 0 array a, bit 1 array b (read from ra / rb,
 // written to wa / wb; b takes a's values where b is not read). A thread reads
 // all its amplitudes before it writes any, so ra may be wa and rb may be wb.
 struct PassGeom {
-    int32_t m, W, tb, pair;
+    int32_t m, W, tb;
     int32_t lq[kMaxQ];  // tile bit j -> amplitude bit
     int32_t oq[kMaxQ];  // tile-index bit k -> amplitude bit
 };
 
+template <int ACC, bool PAIR>
 __global__ __launch_bounds__(256) void k_pass_copy(const float2* ra, const float2* rb, float2* wa, float2* wb,
                                                    const PassGeom g, int rd, int wr) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
     const int t = threadIdx.x;
     if (t >= (1 << (g.m - kRegBits))) return;  // no barriers below
     const unsigned tile = (gridDim.x & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     const unsigned s = tile >> g.tb, tis = tile & ((1u << g.tb) - 1u);
-    size_t base = (size_t)s << g.W;
-    for (int k = 0; k < g.tb; ++k) base |= (size_t)((tis >> k) & 1u) << g.oq[k];
-    const int r0 = g.pair ? 0 : g.m - 4;
-    size_t gT = base;
+    const size_t base = (size_t)s << g.W;  // the sample
+    int gT = 0;                            // amplitude within it
+    for (int k = 0; k < g.tb; ++k) gT |= (int)((tis >> k) & 1u) << g.oq[k];
+    const int r0 = PAIR ? 0 : g.m - 4;
     for (int j = 0, i = 0; j < g.m; ++j) {
         if (j == r0 || j >= g.m - 3) continue;
-        gT |= (size_t)((t >> i) & 1) << g.lq[j];
+        gT |= ((t >> i) & 1) << g.lq[j];
         ++i;
     }
     const int s0 = g.lq[r0], s1 = g.lq[g.m - 3], s2 = g.lq[g.m - 2], s3 = g.lq[g.m - 1];
     float2 va[kRegs], vb[kRegs];
 #pragma unroll
     for (int k = 0; k < kRegs; ++k) va[k] = vb[k] = make_float2(0.f, 0.f);
-    // offset of register pair k, k + 1 (k even); array by array, like the passes
-    auto off = [&](int k) {
-        return gT + ((size_t)((k >> 1) & 1) << s1) + ((size_t)((k >> 2) & 1) << s2) + ((size_t)((k >> 3) & 1) << s3);
+    // offset of register pair k, k + 1 (k even) from the thread's first; array by array, like the passes
+    auto off = [&](int k) { return (((k >> 1) & 1) << s1) + (((k >> 2) & 1) << s2) + (((k >> 3) & 1) << s3); };
+    auto buf = [&](const float2* x) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(x + base), 0, (int)(8u << g.W), 0x00020000);
     };
     auto load = [&](const float2* x, float2 (&v)[kRegs]) {
 #pragma unroll
         for (int k = 0; k < kRegs; k += 2) {
-            const size_t o = off(k);
-            if (g.pair) {
-                const float4 q = *reinterpret_cast<const float4*>(x + o);
-                v[k] = make_float2(q.x, q.y);
-                v[k + 1] = make_float2(q.z, q.w);
+            const int o = off(k);
+            if constexpr (PAIR) {
+                f4v q;
+                if constexpr (ACC) q = __builtin_bit_cast(f4v, (u4)__builtin_amdgcn_raw_buffer_load_b128(buf(x), gT << 3, o << 3, ACC == 2 ? 2 : 0));
+                else q = *(const f4v*)(x + base + gT + o);
+                v[k] = lo2(q);
+                v[k + 1] = hi2(q);
             } else {
-                v[k] = x[o];
-                v[k + 1] = x[o + ((size_t)1 << s0)];
+                for (int h = 0; h < 2; ++h) {
+                    const int oh = o + (h << s0);
+                    if constexpr (ACC) v[k + h] = __builtin_bit_cast(float2, (u2)__builtin_amdgcn_raw_buffer_load_b64(buf(x), gT << 3, oh << 3, 0));
+                    else v[k + h] = x[base + gT + oh];
+                }
             }
         }
     };
     auto store = [&](float2* x, const float2 (&v)[kRegs]) {
 #pragma unroll
         for (int k = 0; k < kRegs; k += 2) {
-            const size_t o = off(k);
-            if (g.pair) {
-                *reinterpret_cast<float4*>(x + o) = make_float4(v[k].x, v[k].y, v[k + 1].x, v[k + 1].y);
+            const int o = off(k);
+            if constexpr (PAIR) {
+                const f4v q = cat2(v[k], v[k + 1]);
+                if constexpr (ACC) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, q), buf(x), gT << 3, o << 3, ACC == 2 ? 2 : 0);
+                else *(f4v*)(x + base + gT + o) = q;
             } else {
-                x[o] = v[k];
-                x[o + ((size_t)1 << s0)] = v[k + 1];
+                for (int h = 0; h < 2; ++h) {
+                    const int oh = o + (h << s0);
+                    if constexpr (ACC) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v[k + h]), buf(x), gT << 3, oh << 3, 0);
+                    else x[base + gT + oh] = v[k + h];
+                }
             }
         }
     };
@@ -3762,12 +3777,15 @@ int qsv_pass_copy(const qsv_plan_t* p, int32_t which, int32_t pass, int64_t B, v
     g.m = m;
     g.W = p->W;
     g.tb = p->W - m;
-    g.pair = pair ? 1 : 0;
     for (int j = 0; j < m; ++j) g.lq[j] = ps.lq[j];
     for (int k = 0; k < g.tb; ++k) g.oq[k] = ps.oq[k];
     const uint64_t tiles = (uint64_t)B << g.tb;
     const int threads = std::max(64, 1 << (m - kRegBits));
-    hipLaunchKernelGGL(k_pass_copy, dim3((unsigned)tiles), dim3(threads), (size_t)lds_bytes, (hipStream_t)stream,
+    const int acc = p->W > kMaxBufferQubits ? 0 : pair && tiles >= stream_tiles(m, which == 0 ? 1 : 2) ? 2 : 1;
+    auto* k = acc == 2 ? k_pass_copy<2, true>
+              : acc == 1 ? (pair ? k_pass_copy<1, true> : k_pass_copy<1, false>)
+                         : (pair ? k_pass_copy<0, true> : k_pass_copy<0, false>);
+    hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(threads), (size_t)lds_bytes, (hipStream_t)stream,
                        (const float2*)ra, (const float2*)rb, wa, wb, g, rd, wr);
     HIP_TRY(hipGetLastError());
     return QSV_OK;
