@@ -156,10 +156,10 @@ def dispatches(d, counter):
 
 
 def _base(name):
-    """Kernel family of a dispatch or of a library record: 'k_pg_adj_vec',
-    'k_pg_adj<float2>' and 'k_pg_adj.sign' all give 'k_pg_adj'."""
-    n = name.split(".")[0].split("<")[0]
-    return n[:-4] if n.endswith("_vec") else n
+    """Kernel family of a dispatch or of a library record: 'k_pg_adj_vec<true>',
+    'k_pg_adj<float2>' and 'k_pg_adj.sign' all give 'k_pg_adj', 'k_pg_apply_one<double2>'
+    gives 'k_pg_apply'."""
+    return re.sub(r"_(vec|one)$", "", name.split(".")[0].split("<")[0])
 
 
 def _match_last(disp, want):
