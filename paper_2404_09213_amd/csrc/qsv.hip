@@ -2146,7 +2146,7 @@ struct PassGeom {
 };
 
 template <int ACC, bool PAIR>
-__global__ __launch_bounds__(256) void k_pass_copy(const float2* ra, const float2* rb, float2* wa, float2* wb,
+__global__ __launch_bounds__(1024) void k_pass_copy(const float2* ra, const float2* rb, float2* wa, float2* wb,
                                                    const PassGeom g, int rd, int wr) {
     typedef unsigned u2 __attribute__((ext_vector_type(2)));
     typedef unsigned u4 __attribute__((ext_vector_type(4)));

@@ -41,3 +41,21 @@ def test_copies_of_large_launches(batch, low_qubits):
     state.zero_()
     p.pass_copy(0, 0, batch, ref)
     assert torch.equal(ref, state)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", [12, 13, 14])
+def test_copies_of_large_tiles(tile):
+    """Workgroups of 256, 512 and 1,024 threads."""
+    import torch
+    print(f"[pass copy] tile={tile}", flush=True)
+    c = inputs.ry_rz_cnot_ring(16, 2)
+    p = binding.Plan(c.n_qubits, c.gates, c.n_weights, c.n_inputs, tile_qubits=tile)
+    state = torch.randn((3, 1 << 16), dtype=torch.complex64, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    ref = state.clone()
+    assert p.info()["n_fwd_passes"] > 1
+    for i in range(1, p.info()["n_fwd_passes"]):
+        p.pass_copy(0, i, 3, state)
+        assert torch.equal(state, ref)
+    p.pass_copy(0, 0, 3, state)
+    assert (state == 0).all()
