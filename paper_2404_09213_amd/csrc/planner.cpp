@@ -921,27 +921,55 @@ struct PassBuilder {
         for (int i = 0; i < kRegBits; ++i) ps.nat_gr[i] = 1 << ps.lq[ps.nat.reg[i]];
     }
 
-    // What a pass appends to the plan, so that it can be taken back.
+    // What a pass appends to the plan: sizes before it, and the entries cut off from there.
     struct Mark {
         size_t stages, ops, terms, gouts, recipes, recipe_gates, factors, out, order;
+        int n_shared, n_ps;
+    };
+    struct Cut {
+        std::vector<DStage> stages;
+        std::vector<DOp> ops;
+        std::vector<DTerm> terms;
+        std::vector<DGOut> gouts;
+        std::vector<DRecipe> recipes;
+        std::vector<int32_t> recipe_gates;
+        std::vector<DFactor> factors;
+        std::vector<DPass> out;
+        std::vector<int32_t> order;
         int n_shared, n_ps;
     };
     Mark mark(const std::vector<DPass>& out, const std::vector<int32_t>& order) const {
         return {p->stages.size(), p->ops.size(), p->terms.size(), p->gouts.size(), p->recipes.size(), p->recipe_gates.size(),
                 p->factors.size(), out.size(), order.size(), p->n_shared_mats[p->dir], p->n_ps_mats[p->dir]};
     }
-    void take_back(const Mark& k, std::vector<DPass>& out, std::vector<int32_t>& order) {
-        p->stages.resize(k.stages);
-        p->ops.resize(k.ops);
-        p->terms.resize(k.terms);
-        p->gouts.resize(k.gouts);
-        p->recipes.resize(k.recipes);
-        p->recipe_gates.resize(k.recipe_gates);
-        p->factors.resize(k.factors);
-        out.resize(k.out);
-        order.resize(k.order);
+    template <class T>
+    static std::vector<T> cut_from(std::vector<T>& v, size_t at) {
+        std::vector<T> c(v.begin() + at, v.end());
+        v.resize(at);
+        return c;
+    }
+    Cut cut(const Mark& k, std::vector<DPass>& out, std::vector<int32_t>& order) {
+        Cut c{cut_from(p->stages, k.stages), cut_from(p->ops, k.ops), cut_from(p->terms, k.terms), cut_from(p->gouts, k.gouts),
+              cut_from(p->recipes, k.recipes), cut_from(p->recipe_gates, k.recipe_gates), cut_from(p->factors, k.factors),
+              cut_from(out, k.out), cut_from(order, k.order), p->n_shared_mats[p->dir], p->n_ps_mats[p->dir]};
         p->n_shared_mats[p->dir] = k.n_shared;
         p->n_ps_mats[p->dir] = k.n_ps;
+        return c;
+    }
+    // Puts a cut back where it was taken from (its entries hold absolute indices).
+    void put(const Cut& c, std::vector<DPass>& out, std::vector<int32_t>& order) {
+        auto add = [](auto& v, const auto& x) { v.insert(v.end(), x.begin(), x.end()); };
+        add(p->stages, c.stages);
+        add(p->ops, c.ops);
+        add(p->terms, c.terms);
+        add(p->gouts, c.gouts);
+        add(p->recipes, c.recipes);
+        add(p->recipe_gates, c.recipe_gates);
+        add(p->factors, c.factors);
+        add(out, c.out);
+        add(order, c.order);
+        p->n_shared_mats[p->dir] = c.n_shared;
+        p->n_ps_mats[p->dir] = c.n_ps;
     }
 
     // A backward pass of the generated kernels takes its 1-qubit runs as rotation cores
@@ -960,15 +988,15 @@ struct PassBuilder {
         const Mark at = mark(out, order);
         emit(gates, dense, m, c, flags, true, out, order);
         const double with_cores = pass_instrs(p, out.back());
-        take_back(at, out, order);
+        const Cut cores = cut(at, out, order);
         emit(gates, dense, m, c, flags, false, out, order);
         const double without = pass_instrs(p, out.back());
         // Near a tie either may win: random circuits' passes take 0.95 to 1.01 of the time with
         // products, the last passes of a ring (estimate 1.01) fill 150 to 158 registers with
         // them, one wave a SIMD less, against 110.
         if (with_cores > 1.015 * without) return;
-        take_back(at, out, order);
-        emit(gates, dense, m, c, flags, true, out, order);
+        cut(at, out, order);
+        put(cores, out, order);
     }
 
     void emit(const std::vector<int>& gates, uint32_t dense, int m, int c, int flags, bool cores,
