@@ -145,9 +145,9 @@ typedef struct {
                             cores (v_mfma_f32_4x4x1_16b: each lane multiplies its own
                             amplitude pair, as a real 4-vector, by the gate's real 4x4
                             form). Bit mask, 0..7: 1 forward kernels (default 1),
-                            2 backward psi, 4 backward lambda (the general 2x2
-                            products left there: rotations are applied as shears);
-                            0 = everything on the vector ALU */
+                            2 backward psi, 4 backward lambda (passes whose gate
+                            runs are taken apart into shears and phases have few
+                            general products); 0 = everything on the vector ALU */
     int32_t weight_remap; /* 1: every weight angle w enters its gate as pi tanh(w)
                             (quantum weight remapping, section "Additional
                             Optimizations": weights mapped into (-pi, pi) by tanh);
